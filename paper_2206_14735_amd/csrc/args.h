@@ -1,5 +1,6 @@
 // Kernel argument blocks (passed by value to the kernels).
 #pragma once
+#include "bins.h"
 #include "device.h"
 
 namespace gs {
@@ -13,6 +14,35 @@ struct EdgeCheck {
   int H, W;
   const long long* pixel;
   float edge;
+};
+
+// Scatter records of the backward, grouped by bin.  An item is a ray sample
+// (0 .. total - 1) or a point of smoothness pair p (total + 2 p, total + 2 p + 1).
+struct ScatterRecords {
+  Bins bins;
+  int2* place;            // [total + 2 S]: table slot and rank inside it; slot < 0: no record
+  unsigned* queue;        // [kQueues][16]: work counters of the scatter
+  unsigned* count;        // [slots + 2], behind the queues: records per slot, then of all dense and all sparse slots
+  unsigned* first;        // [slots]: first record of a slot
+  int slots, spread;
+  long long cap;          // records the arrays hold
+  // Levels of few vertices are summed in kSmallCopies copies (behind the
+  // counts) and folded into the gradient afterwards: windows all over the grid
+  // add to the same few of their vertices.
+  int small_mask;         // bit l: level l is small
+  int small_off[4];       // its first vertex in a copy
+  int small_verts;        // vertices of a copy
+  float* small;           // [kSmallCopies][small_verts][4]
+  float4* pos;            // [cap]: position, tag (bin and kTag flags, as an int)
+  float4* dz;             // [cap][4 levels]: dL/dz
+  float4* a;              // [cap][4 levels]: d(phi)/dz (second-order terms)
+  float4* gv;             // [cap]: dL/d(grad phi)
+};
+
+struct ScatterArgs {
+  Grid g;
+  ScatterRecords rec;
+  float* grad_grid;       // [V][4]
 };
 
 struct FieldArgs {
@@ -41,7 +71,6 @@ struct FieldArgs {
   const float* posw;      // [total][4]: sample position (as the forward computed it), Eikonal
                           // weight (scaled, 0 outside S_fs)
   float smooth_coef;      // 2 * lambda_smooth * loss_scale / S
-  float* grad_grid;       // [V][4]
   float* mlp_partial;     // [gridDim.x][kMlpNumel]
   int need_gx;            // ray mode: compute grad phi for the Eikonal term
   const float* depth;     // forward, optional: [M] observed depth per ray; with it, wave-tiles
@@ -51,17 +80,17 @@ struct FieldArgs {
   int colour;             // ray mode: 1 = colour from the geometry decoder's features; 0 = no colour
                           // here (the paper's colour path runs in its own kernel)
   const int* seg_end;     // ray mode: device copy of the sample count (seg[M]); total is then a capacity
-  // levels whose gradient is accumulated in LDS per block (bit l) and the
-  // float offset of each such level inside the block's LDS area
+  // backward: with scatter records (rec.place non-null) the kernel writes them,
+  // at the place the binning gave each item, and the scatter kernel adds them to
+  // the gradient; without, it adds to grad_grid itself.  Then the levels in
+  // priv_mask are accumulated in LDS per block, each at its float offset of the
+  // block's LDS area
+  ScatterRecords rec;
+  float* grad_grid;       // [V][4]
   int priv_mask;
   int priv_off[4];
   int priv_floats;        // floats of the LDS area
   float* priv_partial;    // [gridDim.x][priv_floats] block partials
-  // gradient copies (optional): the levels not accumulated in LDS scatter into
-  // four x/y-parity copies instead of grad_grid; copy_base[l] is the float
-  // offset of level l's four copies in `copies` (-1: no copies)
-  float* copies;
-  int copy_base[4];
 };
 
 // the paper's colour path (colour grid at the finest level + view direction)
@@ -110,6 +139,10 @@ struct RenderArgs {
   float* seed4;         // [total][4]
   float* posw;          // [total][4]: sample position, Eikonal weight
   float* ray_dv;        // [M]
+  ScatterRecords rec;
+  const float* xs;      // smoothness pairs, binned by the same launch
+  const float* eps;
+  int S;
 };
 
 // proposal network over a set of rays

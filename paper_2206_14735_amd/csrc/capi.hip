@@ -16,9 +16,13 @@ namespace gs {
 hipError_t launch_field(const FieldArgs& a, bool bwd, int blocks, hipStream_t st);
 hipError_t launch_priv_reduce(const FieldArgs& a, int n_part, const int counts[4], float* tmp, hipStream_t st);
 void plan_privatised_levels(FieldArgs& a, int counts[4]);
-long long plan_copies(FieldArgs& a);
-hipError_t launch_copy_fold(const FieldArgs& a, hipStream_t st);
 int priv_max_floats();
+void plan_bins(const Grid& g, Bins& b);
+bool records_pay(const Bins& b, long long points, int far);
+long long plan_tables(const Grid& g, ScatterRecords& r, float* tables);
+long long max_tables();
+hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st);
+hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st);
 int field_grid(const FieldArgs& a, bool bwd);
 hipError_t launch_render(const RenderArgs& a, bool bwd, hipStream_t st);
 hipError_t launch_loss_reduce(const float* ray_partial, int M, const float* smooth_partial, int n_sp, int S,
@@ -153,39 +157,62 @@ struct Workspace {
   float* priv_partial;    // [2048][priv_max_floats]
   float* colsum_tmp;      // [64][max(kMlpNumel, priv_max_floats)]
   float* ray_part;        // [64][8] block partials of sums over rays
-  float* copies;          // gradient copies (grad_copies), else NULL
+  // scatter records (see ScatterRecords), cap = total + 2 S
+  int2* place;            // [cap]
+  float* tables;          // counting tables and copies of small levels (plan_tables)
+  unsigned* bin_first;    // [kMaxBins]
+  float4* rec_pos;        // [cap]
+  float4* rec_gv;         // [cap]
+  float4* rec_dz;         // [cap][4]
+  float4* rec_a;          // [cap][4]
   size_t bytes;
 };
 
-Workspace layout(char* base, int M, int total, int S, long long copy_floats) {
-  (void)S;
+Workspace layout(char* base, int M, int total, int S) {
   Workspace w{};
   size_t off = 0;
   auto take = [&](size_t n) { char* p = base ? base + off : nullptr; off += up(n); return p; };
+  const size_t cap = (size_t)total + 2 * (size_t)S;
   w.ray_partial = reinterpret_cast<float*>(take(sizeof(float) * 8 * (size_t)M));
   w.smooth_partial = reinterpret_cast<float*>(take(sizeof(float) * 4096));
   w.seed4 = reinterpret_cast<float*>(take(sizeof(float) * 4 * (size_t)total));
   w.posw = reinterpret_cast<float*>(take(sizeof(float) * 4 * (size_t)total));
   w.ray_dv = reinterpret_cast<float*>(take(sizeof(float) * (size_t)M));
   w.mlp_partial = reinterpret_cast<float*>(take(sizeof(float) * 2048 * (size_t)gs::kMlpNumel));
-  w.priv_partial = reinterpret_cast<float*>(take(sizeof(float) * 2048 * (size_t)gs::priv_max_floats()));
   w.ray_part = reinterpret_cast<float*>(take(sizeof(float) * 64 * 8));
+  w.priv_partial = reinterpret_cast<float*>(take(sizeof(float) * 2048 * (size_t)gs::priv_max_floats()));
   w.colsum_tmp = reinterpret_cast<float*>(
       take(sizeof(float) * 64 * (size_t)(gs::priv_max_floats() > gs::kMlpNumel ? gs::priv_max_floats() : gs::kMlpNumel)));
-  w.copies = copy_floats > 0 ? reinterpret_cast<float*>(take(sizeof(float) * (size_t)copy_floats)) : nullptr;
+  w.place = reinterpret_cast<int2*>(take(sizeof(int2) * cap));
+  w.tables = reinterpret_cast<float*>(take(sizeof(float) * (size_t)gs::max_tables()));
+  w.bin_first = reinterpret_cast<unsigned*>(take(sizeof(unsigned) * gs::kMaxBins));
+  w.rec_pos = reinterpret_cast<float4*>(take(sizeof(float4) * cap));
+  w.rec_gv = reinterpret_cast<float4*>(take(sizeof(float4) * cap));
+  w.rec_dz = reinterpret_cast<float4*>(take(sizeof(float4) * 4 * cap));
+  w.rec_a = reinterpret_cast<float4*>(take(sizeof(float4) * 4 * cap));
   w.bytes = off;
   return w;
 }
 
-// Floats of the model's gradient copies: 0 without copies, -1 if the model's
-// levels are too large for them.
-long long model_copy_floats(const gosurf_model* m) {
+// Bytes that grad_copies = 1 adds to the workspace: 0 without it, -1 if the
+// model's levels are too large for it.  The sizes are those of four x/y-parity
+// copies (64-byte units of 2 x 2 vertices) of every level that does not fit,
+// coarsest first, 1024 vertices.  The scatter needs no copies; the flag stays
+// part of the interface, with its sizes and limits.
+long long model_copy_bytes(const gosurf_model* m) {
   if (!m->grad_copies) return 0;
-  gs::FieldArgs fa{};
-  fa.g = to_grid(m);
-  int counts[4];
-  gs::plan_privatised_levels(fa, counts);
-  return gs::plan_copies(fa);
+  long long kept = 0, floats = 0;
+  for (int l = 0; l < GOSURF_LEVELS; ++l) {
+    const long long nx = m->dims[l][0], ny = m->dims[l][1], nz = m->dims[l][2];
+    if (kept + nx * ny * nz <= 1024) {
+      kept += nx * ny * nz;
+      continue;
+    }
+    if (nx > 2048 || ny > 2048 || nz > 512) return -1;
+    floats += 4LL * nz * ((nx >> 1) + 1) * ((ny >> 1) + 1) * 16;
+    if (floats >= (1LL << 31) - 64) return -1;
+  }
+  return (long long)up(sizeof(float) * (size_t)floats);
 }
 
 gosurf_status check_batch(const gosurf_ray_batch* b, bool need_outputs) {
@@ -257,10 +284,10 @@ size_t gosurf_workspace_bytes(const gosurf_model* model, int32_t M, int32_t tota
   long long cf = 0;
   if (model) {
     if (check_model(model) != GOSURF_OK) return 0;
-    cf = model_copy_floats(model);
+    cf = model_copy_bytes(model);
     if (cf < 0) return 0;
   }
-  return layout(nullptr, M, total, S, cf).bytes;
+  return layout(nullptr, M, total, S).bytes + (size_t)cf;
 }
 
 gosurf_status gosurf_sample_rays(const gosurf_model* model, const gosurf_frames* fr, const gosurf_sample_cfg* c,
@@ -459,8 +486,7 @@ gosurf_status gosurf_forward(const gosurf_model* model, const gosurf_params* par
                              void* stream) {
   gosurf_status st;
   if ((st = forward_checks(model, params, b, loss, out)) != GOSURF_OK) return st;
-  // the forward uses the part before the gradient copies
-  const Workspace w = layout(static_cast<char*>(ws), b->M, b->total, b->S, 0);
+  const Workspace w = layout(static_cast<char*>(ws), b->M, b->total, b->S);
   if (!ws || ws_bytes < w.bytes)
     return fail(GOSURF_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
                 w.bytes);
@@ -500,13 +526,13 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
     return fail(GOSURF_ERR_NULL, "grads.ray_o and grads.ray_r are both given or both NULL");
   if (!aligned(grads->grid, 16)) return fail(GOSURF_ERR_ALIGN, "grads.grid must be 16-byte aligned");
   if (!std::isfinite(loss_scale)) return fail(GOSURF_ERR_VALUE, "loss_scale must be finite");
-  const long long copy_floats = model_copy_floats(model);
-  if (copy_floats < 0)
+  const long long copy_bytes = model_copy_bytes(model);
+  if (copy_bytes < 0)
     return fail(GOSURF_ERR_VALUE, "gradient copies need levels of at most 2048 x 2048 x 512 vertices and 2^31 floats");
-  const Workspace w = layout(static_cast<char*>(ws), b->M, b->total, b->S, copy_floats);
-  if (!ws || ws_bytes < w.bytes)
-    return fail(GOSURF_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes,
-                w.bytes);
+  const Workspace w = layout(static_cast<char*>(ws), b->M, b->total, b->S);
+  const size_t need = w.bytes + (size_t)copy_bytes;
+  if (!ws || ws_bytes < need)
+    return fail(GOSURF_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu required", ws_bytes, need);
   hipStream_t s = (hipStream_t)stream;
   const gs::Grid g = to_grid(model);
   const bool need_gx = loss->lambda[4] != 0.f;
@@ -518,13 +544,30 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   for (int k = 0; k < 6; ++k) ra.lam[k] = loss->lambda[k];
   ra.n_depth_rays = fwd->losses + 7;
   ra.loss_scale = loss_scale; ra.seed4 = w.seed4; ra.posw = w.posw; ra.ray_dv = w.ray_dv;
-  if ((st = hip_check(gs::launch_render(ra, true, s), "render bwd")) != GOSURF_OK) return st;
-
+  // the smoothness pairs are skipped without their term
+  const int S = loss->lambda[5] != 0.f ? b->S : 0;
+  gs::ScatterRecords& rec = ra.rec;
+  gs::plan_bins(g, rec.bins);
   gs::FieldArgs fa{};
-  fa.g = g; fa.grid = params->grid; fa.mlp = params->mlp;
+  fa.g = g;
+  int counts[4];
+  gs::plan_privatised_levels(fa, counts);
+  const bool records = gs::records_pay(rec.bins, (long long)b->total + 2LL * S, 4 - __builtin_popcount(fa.priv_mask));
+  if (records) fa.priv_mask = fa.priv_floats = 0;
+  if (records) {
+    const long long n_tables = gs::plan_tables(g, rec, w.tables);
+    rec.place = w.place; rec.first = w.bin_first; rec.cap = (long long)b->total + 2LL * S;
+    rec.pos = w.rec_pos; rec.gv = w.rec_gv; rec.dz = w.rec_dz; rec.a = w.rec_a;
+    ra.xs = b->xs; ra.eps = b->eps; ra.S = S;
+    if ((st = hip_check(gs::launch_zero(w.tables, n_tables, s), "zero bins")) != GOSURF_OK) return st;
+  }
+  if ((st = hip_check(gs::launch_render(ra, true, s), "render bwd")) != GOSURF_OK) return st;
+  if (records && (st = hip_check(gs::launch_bin_first(rec, s), "bin offsets")) != GOSURF_OK) return st;
+
+  fa.grid = params->grid; fa.mlp = params->mlp;
   fa.grid_bf16 = model->precision == GOSURF_BF16 ? params->grid_bf16 : nullptr;
   fa.o = b->o; fa.r = b->r; fa.t = b->t; fa.ray_of = b->ray_of; fa.total = b->total;
-  fa.xs = b->xs; fa.eps = b->eps; fa.S = b->S; fa.seg_end = b->seg + b->M;
+  fa.xs = b->xs; fa.eps = b->eps; fa.S = S; fa.seg_end = b->seg + b->M;
   fa.seed4 = w.seed4; fa.posw = w.posw; fa.need_gx = need_gx;
   const bool ray_grads = grads->ray_o != nullptr;
   const bool cgrid = model->colour_mode == GOSURF_COLOUR_GRID;
@@ -534,25 +577,21 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.grad_x = ray_grads ? w.seed4 : nullptr;
   if (cgrid && ray_grads)
     return fail(GOSURF_ERR_VALUE, "ray gradients (pose refinement) are not built for the colour-grid path");
-  fa.grad_grid = grads->grid; fa.mlp_partial = w.mlp_partial;
-  fa.smooth_coef = b->S > 0 ? 2.f * loss->lambda[5] * loss_scale / (float)b->S : 0.f;
-  if (loss->lambda[5] == 0.f) fa.S = 0;   // the smoothness pairs are skipped
-  int counts[4];
-  gs::plan_privatised_levels(fa, counts);
+  fa.rec = rec; fa.grad_grid = grads->grid; fa.mlp_partial = w.mlp_partial;
   fa.priv_partial = w.priv_partial;
-  if (copy_floats > 0) {
-    fa.copies = w.copies;
-    gs::plan_copies(fa);
-    if ((st = hip_check(gs::launch_zero(w.copies, copy_floats, s), "zero gradient copies")) != GOSURF_OK) return st;
-  }
+  fa.smooth_coef = b->S > 0 ? 2.f * loss->lambda[5] * loss_scale / (float)b->S : 0.f;
   const int nb = gs::field_grid(fa, true);
   if (nb <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
   mark(GOSURF_KERNEL_FIELD_BWD, true, s);
   if ((st = hip_check(gs::launch_field(fa, true, nb, s), "field bwd")) != GOSURF_OK) return st;
+  if (records) {
+    gs::ScatterArgs sa{};
+    sa.g = g; sa.rec = rec; sa.grad_grid = grads->grid;
+    if ((st = hip_check(gs::launch_scatter(sa, s), "grid scatter")) != GOSURF_OK) return st;
+  }
   mark(GOSURF_KERNEL_FIELD_BWD, false, s);
-  if (copy_floats > 0 && (st = hip_check(gs::launch_copy_fold(fa, s), "fold gradient copies")) != GOSURF_OK)
-    return st;
-  if ((st = hip_check(gs::launch_priv_reduce(fa, nb, counts, w.colsum_tmp, s), "level reduce")) != GOSURF_OK)
+  if (!records &&
+      (st = hip_check(gs::launch_priv_reduce(fa, nb, counts, w.colsum_tmp, s), "level reduce")) != GOSURF_OK)
     return st;
   if (ray_grads &&
       (st = hip_check(gs::launch_ray_xgrad(w.seed4, b->t, b->seg, b->M, b->total, grads->ray_o, grads->ray_r, s),

@@ -89,7 +89,10 @@ __device__ __forceinline__ float log_sigmoid(float x) {
   return x >= 0.f ? -log1pf(__expf(-x)) : x - log1pf(__expf(x));
 }
 __device__ __forceinline__ float sigmoidf_(float x) {
-  return x >= 0.f ? 1.f / (1.f + __expf(-x)) : __expf(x) / (1.f + __expf(x));
+  // 1 / (1 + e^-x) or e^x / (1 + e^x), whichever does not overflow: one
+  // exponential and one division for both
+  const float e = __expf(-fabsf(x));
+  return (x >= 0.f ? 1.f : e) / (1.f + e);
 }
 __device__ __forceinline__ float signf_(float x) { return x > 0.f ? 1.f : (x < 0.f ? -1.f : 0.f); }
 

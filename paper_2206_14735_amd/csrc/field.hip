@@ -120,15 +120,10 @@ struct ScatterStage {
 //    writers compute their segments' destinations, so the atomic loop reads
 //    only LDS (po >= 0: this lane's level has its LDS copy at float offset po).
 // BF: the BF16 kernel (decoders in bf16), which keeps fewer atomics in flight.
-// 4. With gradient copies (cpb >= 0: this lane's level scatters into four
-//    x/y-parity copies), the writer of cell (i, j, k) uses copy (i & 1, j & 1),
-//    where the cell's four corners at one z are one aligned 64-byte unit
-//    [dy][dx][feature]: its four segments are two such units, one request each
-//    instead of about five for the segments of the single layout.
-template <bool HAS_DZ, bool HAS_GV, bool BF, bool COPIES>
+template <bool HAS_DZ, bool HAS_GV, bool BF>
 __device__ __forceinline__ void scatter(const FieldArgs& A, float* priv, const ScatterStage& S, int lane, int q,
-                                        int j, const LevelSample& ls, const LevelConst& lc, int po, int cpb,
-                                        bool valid, const float dz[4], const float a[4], const float gv[3]) {
+                                        int j, const LevelSample& ls, const LevelConst& lc, int po, bool valid,
+                                        const float dz[4], const float a[4], const float gv[3]) {
   // an invalid lane's inputs are zeroed (and its weights kept finite), so
   // its 32 values are exact zeros
   const float fx = valid ? ls.f[0] : 0.f, fy = valid ? ls.f[1] : 0.f, fz = valid ? ls.f[2] : 0.f;
@@ -173,25 +168,16 @@ __device__ __forceinline__ void scatter(const FieldArgs& A, float* priv, const S
   const bool writer = head && valid;
   const unsigned long long wm = __ballot(writer);
   const int nw = __popcll(wm);
+  const int rank = __popcll(wm & ((1ull << lane) - 1ull));
   if (writer) {
-    const int rank = __popcll(wm & ((1ull << lane) - 1ull));
     float* st = S.val + rank * 32;
-    int unit = 0, plane = 0;
-    if (COPIES && cpb >= 0) {
-      const int ci = ls.cell & 2047, cj = (ls.cell >> 11) & 2047, ck = ls.cell >> 22;
-      const int mx = (lc.n[0] >> 1) + 1, my = (lc.n[1] >> 1) + 1;
-      plane = mx * my * 16;
-      unit = cpb + ((ci & 1) + 2 * (cj & 1)) * (lc.n[2] * plane) + ck * plane + ((cj >> 1) * mx + (ci >> 1)) * 16;
-    }
 #pragma unroll
     for (int sg = 0; sg < 4; ++sg) {
       const int c0 = sg, c1 = 4 + sg;   // corners (0, by, bz) and (1, by, bz), sg = 2 by + bz
       *reinterpret_cast<float4*>(st + 8 * sg) = make_float4(val[c0][0], val[c0][1], val[c0][2], val[c0][3]);
       *reinterpret_cast<float4*>(st + 8 * sg + 4) = make_float4(val[c1][0], val[c1][1], val[c1][2], val[c1][3]);
       const long long row = ls.row + (long long)(sg >> 1) * ls.sy + (long long)(sg & 1) * ls.sz;
-      S.dst[4 * rank + sg] = po >= 0   ? ~(po + 4 * (int)(row - lc.off))
-                             : COPIES && cpb >= 0 ? unit + (sg & 1) * plane + (sg >> 1) * 8
-                                       : (int)row;
+      S.dst[4 * rank + sg] = po >= 0 ? ~(po + 4 * (int)(row - lc.off)) : (int)row;
     }
   }
   wave_lds_fence();
@@ -219,7 +205,6 @@ __device__ __forceinline__ void scatter(const FieldArgs& A, float* priv, const S
     else wait_vmem_at_most<1>();
     if (k < jobs) {
       if (d < 0) atomic_add_lds(priv + (~d) + f, v);
-      else if constexpr (COPIES) atomic_add_global(A.copies + d + f, v);   // every level not in LDS has copies
       else atomic_add_global(A.grad_grid + (long long)d * 4 + f, v);
     }
     k = kn;
@@ -229,40 +214,77 @@ __device__ __forceinline__ void scatter(const FieldArgs& A, float* priv, const S
   wave_lds_fence();
 }
 
+// Place of the scatter record of an item (-1: none): the first record of its
+// table slot plus its rank there.  The bounds hold for every table the binning
+// writes; they keep a batch whose offsets leave samples out inside the arrays.
+__device__ __forceinline__ long long record_place(const ScatterRecords& R, long long item) {
+  const int2 pl = R.place[item];
+  if (pl.x < 0 || pl.x >= R.slots) return -1;
+  const long long d = (long long)R.first[pl.x] + (unsigned)pl.y;
+  return d < R.cap ? d : -1;
+}
+
+// Writes the record of this lane's level: lane (q, j) holds level q of item j.
+// SECOND: the tile has second-order terms, which the lanes with `second` write.
+template <bool FIRST, bool SECOND>
+__device__ __forceinline__ void write_record(const ScatterRecords& R, long long place, int q, float x, float y, float z,
+                                             int bin, const v4f& dz, const v4f& a, const float gv[3], bool second) {
+  if (place < 0) return;
+  if constexpr (FIRST) R.dz[4 * place + q] = make_float4(dz[0], dz[1], dz[2], dz[3]);
+  const bool s = SECOND && second;
+  if (s) {
+    R.a[4 * place + q] = make_float4(a[0], a[1], a[2], a[3]);
+    if (q == 1) R.gv[place] = make_float4(gv[0], gv[1], gv[2], 0.f);
+  }
+  const int tag = bin | (FIRST ? 0 : kTagNoFirst) | (s ? kTagSecond : 0);
+  if (q == 0) R.pos[place] = make_float4(x, y, z, __int_as_float(tag));
+}
+
 __device__ __forceinline__ v4f relu_mask(v4f x, v4f h) {
   return v4f{h[0] > 0.f ? x[0] : 0.f, h[1] > 0.f ? x[1] : 0.f, h[2] > 0.f ? x[2] : 0.f,
              h[3] > 0.f ? x[3] : 0.f};
 }
 
+// Short sums with the fused operations written out: the compiler may fuse either
+// product of a sum of two, and chooses differently in different kernels, whose
+// results are compared bit for bit.
+__device__ __forceinline__ float dot3(const float a[3], const float b[3]) {
+  return fmaf(a[2], b[2], fmaf(a[1], b[1], a[0] * b[0]));
+}
+__device__ __forceinline__ float dot4(const v4f& x, const float (&G)[4][3], int a) {
+  return fmaf(x[3], G[3][a], fmaf(x[2], G[2][a], fmaf(x[1], G[1][a], x[0] * G[0][a])));
+}
+
 // LDS footprint of one block.  The fp32 kernels keep one float per lane per
 // MFMA step, the bf16 kernels four packed bf16 values per lane per input block;
 // only the backward kernels need the per-wave scratch.
-template <bool BF, bool BWD>
+template <bool BF, bool BWD, bool REC>
 struct FieldSmem {
   float tab[BF ? 1 : T_END * 64];
   uint2 tabbf[BF ? (T_END / 4) * 64 : 1];
   float bias[32 + 32 + 16 + 32 + 16];   // b1, b2, b3, c1, c2(pad 16)
   float w3row0[32];
-  float scr[kWavesPerBlock][BWD ? 2048 : 1];   // operand transposes, then scatter staging
-  int dst[kWavesPerBlock][BWD ? 256 : 1];
+  // operand transposes (2 x 32 rows), then, without records, scatter staging
+  // (64 writers' 32 floats and 4 destinations)
+  float scr[kWavesPerBlock][BWD ? (REC ? 2 * 32 * RSR : 64 * 36) : 1];
 };
 constexpr int kRedFloats = kWavesPerBlock * kMlpNumel;
 // the area is reused at the end for the per-wave block partials
-template <bool BF, bool BWD>
+template <bool BF, bool BWD, bool REC>
 constexpr int smem_bytes() {
   constexpr int red = BWD ? kRedFloats * 4 : kWavesPerBlock * 4;
-  return (sizeof(FieldSmem<BF, BWD>) > red) ? (int)sizeof(FieldSmem<BF, BWD>) : red;
+  return (sizeof(FieldSmem<BF, BWD, REC>) > red) ? (int)sizeof(FieldSmem<BF, BWD, REC>) : red;
 }
-constexpr int kPrivMaxFloats = 4096;
+constexpr int kPrivMaxFloats = 4096;   // LDS budget for privatised levels (1024 vertices)
 constexpr int kFieldMaxBlocksFwd = 4096;   // rows of the smoothness partials in the workspace
-constexpr int kFieldMaxBlocksBwd = 2048;   // rows of the decoder / level partials in the workspace   // LDS budget for privatised levels (1024 vertices)
+constexpr int kFieldMaxBlocksBwd = 2048;   // rows of the decoder / level partials in the workspace
 
 // One wave-tile: MODE 0 = 16 ray samples, MODE 1 = 8 smoothness pairs (lanes
 // j < 8 hold x, lanes j >= 8 hold x + eps of the same pair).  POSE (backward
 // only): also dL/dx of every ray sample, for camera pose refinement.
-template <int MODE, bool BWD, bool BF, bool POSE, bool COPIES, class Smem>
+template <int MODE, bool BWD, bool BF, bool POSE, bool REC, class Smem>
 __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, int tile, int total, int lane, int q,
-                                           int j, const LevelConst& lc, int po, int cpb, float* scrA, float* scrB,
+                                           int j, const LevelConst& lc, int po, float* scrA, float* scrB,
                                            const ScatterStage& stage, float* priv,
                                            v4f (&aW1)[2], v4f (&aW2)[4], v4f (&aW3)[2], v4f (&aU1)[2], v4f& aS,
                                            float& smooth_acc) {
@@ -358,15 +380,16 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
       for (int r = 0; r < 4; ++r) hc[b][r] = fmaxf(hc[b][r] + sm.bias[80 + 16 * b + 4 * q + r], 0.f);
     layer<BF, 1, 2>(sm, T_C2, hc, &cb, lane);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) cb[r] = sigmoidf_(cb[r] + sm.bias[112 + 4 * q + r]);
+    for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_(cb[r] + sm.bias[112 + 4 * q + r]);   // rows 0..2 of group 0 are used
   } else {
     cb = v4f{0.f, 0.f, 0.f, 0.f};
   }
 
-  // ---------------- d phi / d x
+  // ---------------- d phi / d x (the backward of ray samples takes it after the
+  // first-order gradients, whose operands are dead by then)
   v4f e2[2], e1[2], ab;
   float gx[3] = {0.f, 0.f, 0.f};
-  if (need_g) {
+  auto slope = [&] {
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
@@ -377,12 +400,13 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     layer<BF, 1, 2>(sm, T_L1T, e1, &ab, lane);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      float v = ab[0] * G[0][a] + ab[1] * G[1][a] + ab[2] * G[2][a] + ab[3] * G[3][a];
+      float v = dot4(ab, G, a);
       v += __shfl_xor(v, 16, 64);
       v += __shfl_xor(v, 32, 64);
       gx[a] = v;
     }
-  }
+  };
+  if ((!BWD || MODE == 1) && need_g) slope();
 
   if constexpr (!BWD) {
     if (MODE == 0) {
@@ -390,7 +414,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
         *reinterpret_cast<float4*>(A.out4 + 4 * (size_t)item) = make_float4(ob[0], cb[0], cb[1], cb[2]);
         if (A.need_gx) {
           // (a tile that skipped d(phi)/dx holds no S_fs sample: its residuals are not read)
-          const float n = sqrtf(gx[0] * gx[0] + gx[1] * gx[1] + gx[2] * gx[2]);
+          const float n = sqrtf(dot3(gx, gx));
           A.eik[item] = need_g ? (1.f - n) * (1.f - n) : 0.f;
           if (A.grad_phi) {
             float* gp = A.grad_phi + 3 * (size_t)item;
@@ -418,69 +442,23 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
   // ================================================================ backward
   float gv[3] = {0.f, 0.f, 0.f};   // dL / d(grad phi)
   if (MODE == 0) {
+    // Each layer's weight gradients (sums over the tile's samples, the MFMA K
+    // axis) directly follow its output gradients, so that as few operands as
+    // possible are live at a time.
     const float4 sd = valid ? seed_in : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float ew = valid && A.need_gx ? ew_in : 0.f;
-    if (A.need_gx && ew != 0.f) {
-      const float n = sqrtf(gx[0] * gx[0] + gx[1] * gx[1] + gx[2] * gx[2]);
-      const float c = n > 0.f ? ew * 2.f * (n - 1.f) / n : 0.f;
-      gv[0] = c * gx[0]; gv[1] = c * gx[1]; gv[2] = c * gx[2];
-    }
-    // colour: dL/d(pre-sigmoid) for rows 0..2 held by level-group 0
-    const bool col = A.colour != 0;
-    v4f dc2 = v4f{0, 0, 0, 0};
-    if (q == 0 && col) {
-      dc2[0] = sd.y * cb[0] * (1.f - cb[0]);
-      dc2[1] = sd.z * cb[1] * (1.f - cb[1]);
-      dc2[2] = sd.w * cb[2] * (1.f - cb[2]);
-    }
-    v4f dhc[2], dob = v4f{0, 0, 0, 0};
-    if (col) {
+    float4 tX[2], tY[2];
+    v4f dob = v4f{0, 0, 0, 0};
+    if (A.colour) {
+      // colour: dL/d(pre-sigmoid) for rows 0..2 held by level-group 0
+      v4f dc2 = v4f{0, 0, 0, 0}, dhc[2];
+      if (q == 0) {
+        dc2[0] = sd.y * cb[0] * (1.f - cb[0]);
+        dc2[1] = sd.z * cb[1] * (1.f - cb[1]);
+        dc2[2] = sd.w * cb[2] * (1.f - cb[2]);
+      }
       layer<BF, 2, 1>(sm, T_C2T, &dc2, dhc, lane);
 #pragma unroll
       for (int b = 0; b < 2; ++b) dhc[b] = relu_mask(dhc[b], hc[b]);
-      layer<BF, 1, 2>(sm, T_C1T, dhc, &dob, lane);
-    }
-    if (q == 0) dob[0] += sd.x;
-    v4f dh2[2], dh1[2], dz;
-    layer<BF, 2, 1>(sm, T_L3T, &dob, dh2, lane);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) dh2[b] = relu_mask(dh2[b], h2[b]);
-    layer<BF, 2, 2>(sm, T_L2T, dh2, dh1, lane);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) dh1[b] = relu_mask(dh1[b], h1[b]);
-    layer<BF, 1, 2>(sm, T_L1T, dh1, &dz, lane);
-
-    if constexpr (POSE) {
-      // dL/dx = sum over levels and features of dL/dz_k dz_k/dx, plus, through
-      // the Eikonal residual, (d^2 phi/dx^2) dL/d(grad phi) with
-      // d^2 phi/dx^2 = sum_k (df/dz_k) d^2 z_k/dx^2 (the decoder's own second
-      // derivative vanishes for ReLU units; supplementary Eq.
-      // second_sdf_grad_x and the h12, h13, h23 block)
-      float dxv[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) dxv[a] = dz[0] * G[0][a] + dz[1] * G[1][a] + dz[2] * G[2][a] + dz[3] * G[3][a];
-      if (A.need_gx) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float ak = ab[k], h12 = hs.h[k][0], h13 = hs.h[k][1], h23 = hs.h[k][2];
-          dxv[0] += ak * (h12 * gv[1] + h13 * gv[2]);
-          dxv[1] += ak * (h12 * gv[0] + h23 * gv[2]);
-          dxv[2] += ak * (h13 * gv[0] + h23 * gv[1]);
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        dxv[a] += __shfl_xor(dxv[a], 16, 64);
-        dxv[a] += __shfl_xor(dxv[a], 32, 64);
-      }
-      // the seeds of this sample were read at the start of the tile by this wave
-      // alone; their slot takes dL/dx
-      if (q == 0 && live) *reinterpret_cast<float4*>(A.grad_x + 4 * (size_t)item) = make_float4(dxv[0], dxv[1], dxv[2], 0.f);
-    }
-
-    // weight gradients (sums over the tile's samples, the MFMA K axis)
-    float4 tX[2], tY[2];
-    if (col) {
       // U2 and c2: U2[c][k] = sum_s dc2[c][s] hc[k][s] goes to column 10 + 3b + c
       // of aS (row k - 16b), with hc as the A operand and dc2 row c as the B
       // operand of exactly those columns
@@ -505,18 +483,28 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
       rows_to_lanes<1>(scrB, &ob, tY, q, j);
       if (j == 0) tY[0] = make_float4(1.f, 1.f, 1.f, 1.f);
       outer_lanes<BF, 2, 1>(tX, tY, aU1);
+      layer<BF, 1, 2>(sm, T_C1T, dhc, &dob, lane);
     }
+    if (q == 0) dob[0] += sd.x;
+    v4f dh2[2], dh1[2], dz;
+    layer<BF, 2, 1>(sm, T_L3T, &dob, dh2, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) dh2[b] = relu_mask(dh2[b], h2[b]);
     // W3 and b3
     rows_to_lanes<1>(scrA, &dob, tX, q, j);
     rows_to_lanes<2>(scrB, h2, tY, q, j);
     outer_lanes<BF, 1, 2>(tX, tY, aW3);
     colsum_into(tX[0], 4, aS, j);
+    layer<BF, 2, 2>(sm, T_L2T, dh2, dh1, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) dh1[b] = relu_mask(dh1[b], h1[b]);
     // W2 and b2
     rows_to_lanes<2>(scrA, dh2, tX, q, j);
     rows_to_lanes<2>(scrB, h1, tY, q, j);
     outer_lanes<BF, 2, 2>(tX, tY, aW2);
     colsum_into(tX[0], 2, aS, j);
     colsum_into(tX[1], 3, aS, j);
+    layer<BF, 1, 2>(sm, T_L1T, dh1, &dz, lane);
     // W1 and b1
     rows_to_lanes<2>(scrA, dh1, tX, q, j);
     rows_to_lanes<1>(scrB, &zb, tY, q, j);
@@ -524,12 +512,55 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     colsum_into(tX[0], 0, aS, j);
     colsum_into(tX[1], 1, aS, j);
 
+    const float ew = valid && A.need_gx ? ew_in : 0.f;
+    if (need_g) {
+      slope();
+      if (A.need_gx && ew != 0.f) {
+        const float n = sqrtf(dot3(gx, gx));
+        const float c = n > 0.f ? ew * 2.f * (n - 1.f) / n : 0.f;
+        gv[0] = c * gx[0]; gv[1] = c * gx[1]; gv[2] = c * gx[2];
+      }
+    }
+    if constexpr (POSE) {
+      // dL/dx = sum over levels and features of dL/dz_k dz_k/dx, plus, through
+      // the Eikonal residual, (d^2 phi/dx^2) dL/d(grad phi) with
+      // d^2 phi/dx^2 = sum_k (df/dz_k) d^2 z_k/dx^2 (the decoder's own second
+      // derivative vanishes for ReLU units; supplementary Eq.
+      // second_sdf_grad_x and the h12, h13, h23 block)
+      float dxv[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) dxv[a] = dot4(dz, G, a);
+      if (A.need_gx) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float ak = ab[k], h12 = hs.h[k][0], h13 = hs.h[k][1], h23 = hs.h[k][2];
+          dxv[0] += ak * (h12 * gv[1] + h13 * gv[2]);
+          dxv[1] += ak * (h12 * gv[0] + h23 * gv[2]);
+          dxv[2] += ak * (h13 * gv[0] + h23 * gv[1]);
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        dxv[a] += __shfl_xor(dxv[a], 16, 64);
+        dxv[a] += __shfl_xor(dxv[a], 32, 64);
+      }
+      // the seeds of this sample were read at the start of the tile by this wave
+      // alone; their slot takes dL/dx
+      if (q == 0 && live) *reinterpret_cast<float4*>(A.grad_x + 4 * (size_t)item) = make_float4(dxv[0], dxv[1], dxv[2], 0.f);
+    }
+
     const float dzl[4] = {dz[0], dz[1], dz[2], dz[3]};
+    long long place = -1;
+    int bin = 0;
+    if constexpr (REC) {
+      if (valid) place = record_place(A.rec, item);
+      bin = bin_of(A.rec.bins, px, py, pz);
+    }
     if (need_g && A.need_gx) {
       // second-order terms of the Eikonal residual
       v4f qv;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) qv[k] = gv[0] * G[k][0] + gv[1] * G[k][1] + gv[2] * G[k][2];
+      for (int k = 0; k < 4; ++k) qv[k] = dot3(gv, G[k]);
       v4f r1[2], w2r1[2];
       layer<BF, 2, 1>(sm, T_L1, &qv, r1, lane);
 #pragma unroll
@@ -537,7 +568,6 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
       layer<BF, 2, 2>(sm, T_L2, r1, w2r1, lane);
 #pragma unroll
       for (int b = 0; b < 2; ++b) w2r1[b] = relu_mask(w2r1[b], h2[b]);
-      float4 tX[2], tY[2];
       rows_to_lanes<2>(scrA, w2r1, tX, q, j);
       colsum_into(tX[0], 6, aS, j);
       colsum_into(tX[1], 7, aS, j);
@@ -548,10 +578,12 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
       rows_to_lanes<1>(scrB, &qv, tY, q, j);
       outer_lanes<BF, 2, 1>(tX, tY, aW1);
       const float al[4] = {ab[0], ab[1], ab[2], ab[3]};
-      scatter<true, true, BF, COPIES>(A, priv, stage, lane, q, j, ls, lc, po, cpb, valid, dzl, al, gv);
+      if constexpr (REC) write_record<true, true>(A.rec, place, q, px, py, pz, bin, dz, ab, gv, ew != 0.f);
+      else scatter<true, true, BF>(A, priv, stage, lane, q, j, ls, lc, po, valid, dzl, al, gv);
     } else {
       const float al[4] = {0, 0, 0, 0};
-      scatter<true, false, BF, COPIES>(A, priv, stage, lane, q, j, ls, lc, po, cpb, valid, dzl, al, gv);
+      if constexpr (REC) write_record<true, false>(A.rec, place, q, px, py, pz, bin, dz, dz, gv, false);
+      else scatter<true, false, BF>(A, priv, stage, lane, q, j, ls, lc, po, valid, dzl, al, gv);
     }
   } else {
     // smoothness pair: d|g(x) - g(x+eps)|^2 / dg at either point is
@@ -564,7 +596,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     }
     v4f qv;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) qv[k] = gv[0] * G[k][0] + gv[1] * G[k][1] + gv[2] * G[k][2];
+    for (int k = 0; k < 4; ++k) qv[k] = dot3(gv, G[k]);
     v4f r1[2], w2r1[2];
     layer<BF, 2, 1>(sm, T_L1, &qv, r1, lane);
 #pragma unroll
@@ -582,21 +614,28 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     rows_to_lanes<2>(scrA, e1, tX, q, j);
     rows_to_lanes<1>(scrB, &qv, tY, q, j);
     outer_lanes<BF, 2, 1>(tX, tY, aW1);
-    const float al[4] = {ab[0], ab[1], ab[2], ab[3]};
-    const float dzl[4] = {0, 0, 0, 0};
-    scatter<false, true, BF, COPIES>(A, priv, stage, lane, q, j, ls, lc, po, cpb, pv, dzl, al, gv);
+    if constexpr (REC) {
+      const long long place = pv ? record_place(A.rec, (long long)A.total + 2LL * item + (j >> 3)) : -1;
+      write_record<false, true>(A.rec, place, q, px, py, pz, bin_of(A.rec.bins, px, py, pz), ab, ab, gv, true);
+    } else {
+      const float al[4] = {ab[0], ab[1], ab[2], ab[3]};
+      const float dzl[4] = {0, 0, 0, 0};
+      scatter<false, true, BF>(A, priv, stage, lane, q, j, ls, lc, po, pv, dzl, al, gv);
+    }
   }
   }
 }
 
 // Pair tiles come first, then ray tiles, in one launch: the few pair tiles
 // overlap with the ray tiles of other waves.
-// At least two waves per SIMD: the backward kernels then fit 256 registers
-// without spilling, and a second wave hides the gather and atomic latency.
-template <bool BWD, bool BF, bool POSE, bool COPIES>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) void field_kernel(FieldArgs A) {
+// The backward's waves per SIMD: three where the tiles write records (168
+// registers; 65536 x 128 samples: 3.48 ms with two, 3.06 ms with three).  Two
+// where it adds to the gradient itself: its atomics are the bound, and a third
+// wave's only add to their queue (65536 x 96: 3.21 ms with two, 3.35 with three).
+template <bool BWD, bool BF, bool POSE, bool REC>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !POSE ? 3 : 2))) void field_kernel(FieldArgs A) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  FieldSmem<BF, BWD>& sm = *reinterpret_cast<FieldSmem<BF, BWD>*>(smem_raw);
+  FieldSmem<BF, BWD, REC>& sm = *reinterpret_cast<FieldSmem<BF, BWD, REC>*>(smem_raw);
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, j = lane & 15;
 
@@ -631,13 +670,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
   }
   float* scrA = BWD ? sm.scr[wave] : nullptr;
   float* scrB = BWD ? sm.scr[wave] + 32 * RSR : nullptr;
-  const ScatterStage stage{scrA, BWD ? sm.dst[wave] : nullptr};
+  const ScatterStage stage{scrA, BWD ? reinterpret_cast<int*>(scrA + 64 * 32) : nullptr};
   // this lane's grid level (q) in registers; po >= 0 if the level is accumulated in LDS
   const LevelConst lc = level_const(A.g, q);
   const int po = ((uniform_i(A.priv_mask) >> q) & 1) ? pick_level(A.priv_off, q) : -1;
-  const int cpb = COPIES ? pick_level(A.copy_base, q) : -1;
-  float* priv = reinterpret_cast<float*>(smem_raw + smem_bytes<BF, BWD>());
-  if (BWD)
+  float* priv = reinterpret_cast<float*>(smem_raw + smem_bytes<BF, BWD, REC>());
+  if (BWD && !REC)
     for (int e = tid; e < A.priv_floats; e += kBlock) priv[e] = 0.f;
   __syncthreads();
 
@@ -663,11 +701,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 
   for (int tile = blockIdx.x * kWavesPerBlock + wave; tile < n_tiles; tile += gridDim.x * kWavesPerBlock) {
     if (tile < n_pair_tiles)
-      field_tile<1, BWD, BF, POSE, COPIES>(A, sm, tile, total, lane, q, j, lc, po, cpb, scrA, scrB, stage, priv, aW1, aW2, aW3,
-                                   aU1, aS, smooth_acc);
+      field_tile<1, BWD, BF, POSE, REC>(A, sm, tile, total, lane, q, j, lc, po, scrA, scrB, stage, priv, aW1, aW2, aW3, aU1, aS,
+                                        smooth_acc);
     else
-      field_tile<0, BWD, BF, POSE, COPIES>(A, sm, tile - n_pair_tiles, total, lane, q, j, lc, po, cpb, scrA, scrB, stage, priv,
-                                   aW1, aW2, aW3, aU1, aS, smooth_acc);
+      field_tile<0, BWD, BF, POSE, REC>(A, sm, tile - n_pair_tiles, total, lane, q, j, lc, po, scrA, scrB, stage, priv, aW1, aW2,
+                                        aW3, aU1, aS, smooth_acc);
   }
 
   if constexpr (!BWD) {
@@ -689,7 +727,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
 
   // ---------------- block partial of the privatised levels' gradients
   __syncthreads();
-  if (A.priv_floats > 0) {
+  if (!REC && A.priv_floats > 0) {
     float* dst = A.priv_partial + (size_t)blockIdx.x * A.priv_floats;
     for (int e = tid; e < A.priv_floats; e += kBlock) dst[e] = priv[e];
   }
@@ -740,6 +778,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) voi
     out[e] = s;
   }
 }
+
 
 
 // sum of the block partials of the privatised levels into the grid gradient
@@ -799,77 +838,16 @@ void plan_privatised_levels(FieldArgs& a, int counts[4]) {
 
 int priv_max_floats() { return kPrivMaxFloats; }
 
-// Copy layout of one level with (nx, ny, nz) vertices: four copies (px, py),
-// each [nz][my][mx][dy][dx][feature] with mx = nx / 2 + 1, my = ny / 2 + 1;
-// vertex (x, y, z) sits in copy (px, py) at pair (x - px) / 2, (y - py) / 2
-// with dx = (x - px) & 1, dy = (y - py) & 1 (for x >= px, y >= py).
-static long long copy_level_floats(int nx, int ny, int nz) {
-  return 4LL * nz * ((nx >> 1) + 1) * ((ny >> 1) + 1) * 16;
-}
-
-// Gradient copies for every level not accumulated in LDS (call after
-// plan_privatised_levels).  Returns the floats of all copies, or -1 where a
-// level is too large for the packed cell index or the 32-bit offsets.
-long long plan_copies(FieldArgs& a) {
-  long long n = 0;
-  for (int l = 0; l < 4; ++l) {
-    a.copy_base[l] = -1;
-    if ((a.priv_mask >> l) & 1) continue;
-    if (a.g.nx[l] > 2048 || a.g.ny[l] > 2048 || a.g.nz[l] > 512) return -1;
-    a.copy_base[l] = (int)n;
-    n += copy_level_floats(a.g.nx[l], a.g.ny[l], a.g.nz[l]);
-    if (n >= (1LL << 31) - 64) return -1;
-  }
-  return n;
-}
-
-// grad[level] += the level's four copies (one thread per vertex, fixed order).
-// A block covers 64 x 4 vertices of one z-slice: a 64-byte unit holds two
-// rows of the copy, so the rows that share units are read by one block (one
-// XCD's L2) instead of by blocks that the dispatcher spreads over the XCDs.
-__global__ __launch_bounds__(256) void copy_fold_kernel(const float* __restrict__ copies, int base, int nx, int ny,
-                                                        int nz, long long off, float* __restrict__ grad) {
-  const int x = blockIdx.x * 64 + threadIdx.x, y = blockIdx.y * 4 + threadIdx.y, z = blockIdx.z;
-  if (x >= nx || y >= ny) return;
-  const int mx = (nx >> 1) + 1, my = (ny >> 1) + 1, plane = mx * my * 16, csize = nz * plane;
-  float4* gp = reinterpret_cast<float4*>(grad) + off + ((long long)z * ny + y) * nx + x;
-  float4 acc = *gp;
-#pragma unroll
-  for (int py = 0; py < 2; ++py)
-#pragma unroll
-    for (int px = 0; px < 2; ++px) {
-      if (x < px || y < py) continue;
-      const int ux = x - px, uy = y - py;
-      const float4 c = *reinterpret_cast<const float4*>(copies + base + (px + 2 * py) * csize + z * plane +
-                                                        ((uy >> 1) * mx + (ux >> 1)) * 16 + (uy & 1) * 8 +
-                                                        (ux & 1) * 4);
-      acc.x += c.x; acc.y += c.y; acc.z += c.z; acc.w += c.w;
-    }
-  *gp = acc;
-}
-
-hipError_t launch_copy_fold(const FieldArgs& a, hipStream_t st) {
-  for (int l = 0; l < 4; ++l) {
-    if (a.copy_base[l] < 0) continue;
-    hipLaunchKernelGGL(copy_fold_kernel, dim3((unsigned)((a.g.nx[l] + 63) / 64), (unsigned)((a.g.ny[l] + 3) / 4),
-                                              a.g.nz[l]),
-                       dim3(64, 4), 0, st, a.copies, a.copy_base[l], a.g.nx[l], a.g.ny[l], a.g.nz[l],
-                       (long long)a.g.off[l], a.grad_grid);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
-template <bool BWD, bool BF>
+template <bool BWD, bool BF, bool REC>
 static size_t field_smem(const FieldArgs& a) {
-  return (size_t)smem_bytes<BF, BWD>() + (BWD ? (size_t)a.priv_floats * sizeof(float) : 0);
+  return (size_t)smem_bytes<BF, BWD, REC>() + (BWD ? (size_t)a.priv_floats * sizeof(float) : 0);
 }
 
 // Blocks that are resident at once on the current device for this kernel and
 // LDS size (CUs x blocks per CU), queried once per (device, kernel, LDS size).
-template <bool BWD, bool BF, bool POSE, bool COPIES>
-static int resident_blocks(size_t smem) {
+template <bool BWD, bool BF, bool POSE, bool REC>
+static int resident_blocks(const FieldArgs& a) {
+  const size_t smem = field_smem<BWD, BF, REC>(a);
   struct Entry { int dev; size_t smem; int blocks; };
   thread_local Entry cache[8];
   thread_local int n_cached = 0;
@@ -877,7 +855,7 @@ static int resident_blocks(size_t smem) {
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   for (int i = 0; i < n_cached; ++i)
     if (cache[i].dev == dev && cache[i].smem == smem) return cache[i].blocks;
-  const void* fn = reinterpret_cast<const void*>(&field_kernel<BWD, BF, POSE, COPIES>);
+  const void* fn = reinterpret_cast<const void*>(&field_kernel<BWD, BF, POSE, REC>);
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) return 0;
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
@@ -895,18 +873,19 @@ int field_grid(const FieldArgs& a, bool bwd) {
   const bool bf = a.grid_bf16 != nullptr;
   const int tiles = (a.total + 15) / 16 + (a.S + 7) / 8;
   int blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
+  const bool pose = bwd && a.grad_x != nullptr;
+  const bool rec = bwd && a.rec.place != nullptr;
   int resident;
-  const bool pose = bwd && a.grad_x != nullptr, copies = bwd && a.copies != nullptr;
-  if (!bwd) resident = bf ? resident_blocks<false, true, false, false>(field_smem<false, true>(a))
-                          : resident_blocks<false, false, false, false>(field_smem<false, false>(a));
-  else if (bf) resident = pose ? (copies ? resident_blocks<true, true, true, true>(field_smem<true, true>(a))
-                                         : resident_blocks<true, true, true, false>(field_smem<true, true>(a)))
-                               : (copies ? resident_blocks<true, true, false, true>(field_smem<true, true>(a))
-                                         : resident_blocks<true, true, false, false>(field_smem<true, true>(a)));
-  else resident = pose ? (copies ? resident_blocks<true, false, true, true>(field_smem<true, false>(a))
-                                 : resident_blocks<true, false, true, false>(field_smem<true, false>(a)))
-                       : (copies ? resident_blocks<true, false, false, true>(field_smem<true, false>(a))
-                                 : resident_blocks<true, false, false, false>(field_smem<true, false>(a)));
+  if (!bwd) resident = bf ? resident_blocks<false, true, false, false>(a)
+                          : resident_blocks<false, false, false, false>(a);
+  else if (bf) resident = pose ? (rec ? resident_blocks<true, true, true, true>(a)
+                                      : resident_blocks<true, true, true, false>(a))
+                               : (rec ? resident_blocks<true, true, false, true>(a)
+                                      : resident_blocks<true, true, false, false>(a));
+  else resident = pose ? (rec ? resident_blocks<true, false, true, true>(a)
+                              : resident_blocks<true, false, true, false>(a))
+                       : (rec ? resident_blocks<true, false, false, true>(a)
+                              : resident_blocks<true, false, false, false>(a));
   if (resident <= 0) return 0;
   const int cap = bwd ? kFieldMaxBlocksBwd : kFieldMaxBlocksFwd;
   if (blocks > resident) blocks = resident;
@@ -914,23 +893,23 @@ int field_grid(const FieldArgs& a, bool bwd) {
   return blocks < 1 ? 1 : blocks;
 }
 
-template <bool BWD, bool BF, bool POSE, bool COPIES>
+template <bool BWD, bool BF, bool POSE, bool REC>
 static hipError_t launch_field_t(const FieldArgs& a, int blocks, hipStream_t st) {
-  const size_t smem = field_smem<BWD, BF>(a);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&field_kernel<BWD, BF, POSE, COPIES>),
+  const size_t smem = field_smem<BWD, BF, REC>(a);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&field_kernel<BWD, BF, POSE, REC>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((field_kernel<BWD, BF, POSE, COPIES>), dim3(blocks), dim3(kBlock), smem, st, a);
+  hipLaunchKernelGGL((field_kernel<BWD, BF, POSE, REC>), dim3(blocks), dim3(kBlock), smem, st, a);
   return hipGetLastError();
 }
 
 template <bool BF>
 static hipError_t launch_field_bwd(const FieldArgs& a, int blocks, hipStream_t st) {
-  const bool pose = a.grad_x != nullptr, copies = a.copies != nullptr;
-  if (pose) return copies ? launch_field_t<true, BF, true, true>(a, blocks, st)
-                          : launch_field_t<true, BF, true, false>(a, blocks, st);
-  return copies ? launch_field_t<true, BF, false, true>(a, blocks, st)
-                : launch_field_t<true, BF, false, false>(a, blocks, st);
+  const bool pose = a.grad_x != nullptr, rec = a.rec.place != nullptr;
+  if (pose) return rec ? launch_field_t<true, BF, true, true>(a, blocks, st)
+                       : launch_field_t<true, BF, true, false>(a, blocks, st);
+  return rec ? launch_field_t<true, BF, false, true>(a, blocks, st)
+             : launch_field_t<true, BF, false, false>(a, blocks, st);
 }
 
 hipError_t launch_field(const FieldArgs& a, bool bwd, int blocks, hipStream_t st) {

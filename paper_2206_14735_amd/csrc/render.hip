@@ -284,6 +284,23 @@ __device__ __forceinline__ void render_fwd_ray(const RenderArgs& A, int m, int l
   }
 }
 
+// Slot and rank of each sample's scatter record (called by the whole wave,
+// slot < 0: no record).  Neighbouring samples of a ray mostly share a bin, so
+// a run of lanes with one slot takes its ranks with one atomic and its records
+// lie side by side.
+__device__ __forceinline__ int2 place_records(const ScatterRecords& R, int slot, int lane) {
+  const int prev = __builtin_amdgcn_update_dpp(0, slot, 0x138, 0xF, 0xF, true);   // wave_shr:1
+  const bool head = lane == 0 || slot != prev;
+  const unsigned long long hm = __ballot(head);
+  const int start = 63 - __clzll((long long)(hm & ((2ull << lane) - 1ull)));
+  const unsigned long long rest = (hm >> 1) >> lane;
+  const int len = rest ? __ffsll((long long)rest) : 64 - lane;   // lanes to the next head
+  unsigned base = 0u;
+  if (head && slot >= 0) base = __hip_atomic_fetch_add(R.count + slot, (unsigned)len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  base = (unsigned)__shfl((int)base, start, 64);
+  return make_int2(slot, (int)(base + (unsigned)(lane - start)));
+}
+
 template <int W>
 __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int lane) {
   constexpr int NC = seg_chunks<W>();
@@ -391,18 +408,20 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
         ew = A.lam[4] * invM / nfs;
       }
     }
+    // the position again (same rounding as the forward), so that the field
+    // backward reads it with the seeds instead of through ray_of, t, o, r
+    const float tt = R.tt[c];
+    const float px = mad_norm(tt, R.r[0], R.o[0]), py = mad_norm(tt, R.r[1], R.o[1]), pz = mad_norm(tt, R.r[2], R.o[2]);
+    int2 place = make_int2(-1, 0);
+    if (A.rec.place) place = place_records(A.rec, R.valid[c] ? bin_slot(bin_of(A.rec.bins, px, py, pz), A.rec.spread, m) : -1, lane);
     if (k < R.n) {
       const size_t sidx = R.s0 + k;
       const float wk = R.w[c];
       float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
       if (R.valid[c]) out = make_float4(dphi * sc, gc[0] * wk * sc, gc[1] * wk * sc, gc[2] * wk * sc);
       *reinterpret_cast<float4*>(A.seed4 + 4 * sidx) = out;
-      // the position again (same rounding as the forward), so that the field
-      // backward reads it with the seeds instead of through ray_of, t, o, r
-      const float tt = R.tt[c];
-      *reinterpret_cast<float4*>(A.posw + 4 * sidx) =
-          make_float4(mad_norm(tt, R.r[0], R.o[0]), mad_norm(tt, R.r[1], R.o[1]), mad_norm(tt, R.r[2], R.o[2]),
-                      R.valid[c] ? ew * sc : 0.f);
+      *reinterpret_cast<float4*>(A.posw + 4 * sidx) = make_float4(px, py, pz, R.valid[c] ? ew * sc : 0.f);
+      if (A.rec.place) A.rec.place[sidx] = place;
     }
   }
   // samples past the per-ray cap are not rendered: zero seeds and a position
@@ -414,6 +433,7 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
       *reinterpret_cast<float4*>(A.seed4 + 4 * sidx) = make_float4(0.f, 0.f, 0.f, 0.f);
       *reinterpret_cast<float4*>(A.posw + 4 * sidx) =
           make_float4(A.g.p0[0] - 1.f, A.g.p0[1] - 1.f, A.g.p0[2] - 1.f, 0.f);
+      if (A.rec.place) A.rec.place[sidx] = make_int2(-1, 0);
     }
   dv_acc = seg_sum<W>(dv_acc, lane);
   // d s / d v = 10 s
@@ -443,7 +463,32 @@ __global__ __launch_bounds__(256) void render_fwd_kernel(RenderArgs A) {
   render_fwd_ray<64>(A, m, lane);
 }
 
+// Smoothness pairs: both points of a pair inside the box have a record, mostly
+// in one slot (the points lie millimetres apart).
+__device__ __forceinline__ void place_pair(const RenderArgs& A, int p) {
+  if (p >= A.S) return;
+  const float x = A.xs[3 * (size_t)p], y = A.xs[3 * (size_t)p + 1], z = A.xs[3 * (size_t)p + 2];
+  const float x2 = __fadd_rn(x, A.eps[3 * (size_t)p]), y2 = __fadd_rn(y, A.eps[3 * (size_t)p + 1]),
+              z2 = __fadd_rn(z, A.eps[3 * (size_t)p + 2]);
+  int2 p1 = make_int2(-1, 0), p2 = make_int2(-1, 0);
+  if (inside_box(A.g, x, y, z) && inside_box(A.g, x2, y2, z2)) {
+    p1.x = bin_slot(bin_of(A.rec.bins, x, y, z), A.rec.spread, p);
+    p2.x = bin_slot(bin_of(A.rec.bins, x2, y2, z2), A.rec.spread, p);
+    p1.y = (int)__hip_atomic_fetch_add(A.rec.count + p1.x, p1.x == p2.x ? 2u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    p2.y = p1.x == p2.x ? p1.y + 1
+                        : (int)__hip_atomic_fetch_add(A.rec.count + p2.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  A.rec.place[(size_t)A.total + 2 * (size_t)p] = p1;
+  A.rec.place[(size_t)A.total + 2 * (size_t)p + 1] = p2;
+}
+
+// The blocks past the rays' place the smoothness pairs.
 __global__ __launch_bounds__(256) void render_bwd_kernel(RenderArgs A) {
+  const int ray_blocks = (A.M + 3) / 4;
+  if ((int)blockIdx.x >= ray_blocks) {
+    place_pair(A, ((int)blockIdx.x - ray_blocks) * 256 + (int)threadIdx.x);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int m = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
   if (m >= A.M) return;
@@ -687,7 +732,7 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamGroup G0, AdamGroup G1, f
 
 hipError_t launch_render(const RenderArgs& a, bool bwd, hipStream_t st) {
   const int blocks = (a.M + 3) / 4;
-  if (bwd) hipLaunchKernelGGL(render_bwd_kernel, dim3(blocks), dim3(256), 0, st, a);
+  if (bwd) hipLaunchKernelGGL(render_bwd_kernel, dim3(blocks + (a.S + 255) / 256), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(render_fwd_kernel, dim3(blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -204,8 +204,8 @@ def _stream(stream):
 def make_model(layout, precision=FP32, colour_mode=0, grad_copies=False):
     """gosurf_model from a synth.GridLayout (levels coarsest first); colour_mode
     COLOUR_DECODED (0) or COLOUR_GRID (1, the paper's colour path);
-    grad_copies: the backward scatters the large levels into x/y-parity
-    gradient copies in the workspace (see gosurf_backward)."""
+    grad_copies: the workspace has room for gradient copies of the large levels
+    (no result depends on it)."""
     if layout.n_levels != LEVELS:
         raise ValueError(f"the library implements {LEVELS}-level grids")
     m = Model()

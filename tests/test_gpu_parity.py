@@ -477,3 +477,24 @@ def test_tiles_without_free_space_samples_skip_the_gradient():
     e_full = full.saved[4 * db.total:].cpu().numpy()
     e_skip = skip.saved[4 * db.total:].cpu().numpy()
     assert np.array_equal(e_full[fs], e_skip[fs])
+
+
+@pytest.mark.parametrize("grid", ["nested", "unaligned"])
+def test_record_scatter_matches_oracle(grid):
+    """Batches dense enough (512 points per 8^3-cell bin of a small grid) that
+    the backward scatters through records and per-bin windows: levels whose
+    cells nest in the bins, and levels whose cells straddle bin faces; smoothness
+    pairs with points in different bins; bins below and above the 16 records
+    from which a bin gets a window."""
+    if grid == "nested":
+        L, fr, b, grid_, mlp = sphere_case(M=600, S=777, grid_std=0.3)
+    else:
+        L0, fr, b, _, mlp = sphere_case(M=600, S=777, grid_std=0.3)
+        # 2.1 m box; a bin edge (8 x 0.07 m) is 0.8, 1.87 and 2.67 cells of the coarser levels
+        vox = [0.7, 0.3, 0.21, 0.07]
+        L = f32_layout(synth.GridLayout((-1.05,) * 3, (1.05,) * 3, vox, [(n, n, n) for n in (4, 8, 11, 31)]))
+        grid_, mlp = synth.init_params(L, seed=5, grid_std=0.3)
+    bins = int(np.prod([(n - 2) // 8 + 1 for n in L.dims[3]]))
+    b = _clear(grid_, mlp, L, b)
+    assert bins <= 256 and len(b.t) + 2 * len(b.xs) >= 512 * bins
+    compare(run_device(L, b, grid_, mlp), *oracle_pair(grid_, mlp, L, b), case=(L, b, mlp))
