@@ -88,11 +88,24 @@ __device__ __forceinline__ float log_sigmoid(float x) {
   // log(1 / (1 + e^-x)) = -softplus(-x), evaluated without overflow
   return x >= 0.f ? -log1pf(__expf(-x)) : x - log1pf(__expf(x));
 }
+// a / b for b in [1, 2] and 0 <= a <= 1: no operand needs scaling, so a
+// reciprocal, one Newton step and one residual correction replace the general
+// division (6 instructions instead of 11); within an ulp of the exact quotient.
+__device__ __forceinline__ float div_near_one(float a, float b) {
+  float y = __builtin_amdgcn_rcpf(b);
+  y = fmaf(fmaf(-b, y, 1.f), y, y);
+  const float q = a * y;
+  return fmaf(fmaf(-b, q, a), y, q);
+}
+// ROUNDED: the quotient correctly rounded (where it goes on into BF16 operands,
+// which a last bit can move by 2^-9).
+template <bool ROUNDED = false>
 __device__ __forceinline__ float sigmoidf_(float x) {
   // 1 / (1 + e^-x) or e^x / (1 + e^x), whichever does not overflow: one
   // exponential and one division for both
   const float e = __expf(-fabsf(x));
-  return (x >= 0.f ? 1.f : e) / (1.f + e);
+  if constexpr (ROUNDED) return (x >= 0.f ? 1.f : e) / (1.f + e);
+  else return div_near_one(x >= 0.f ? 1.f : e, 1.f + e);
 }
 __device__ __forceinline__ float signf_(float x) { return x > 0.f ? 1.f : (x < 0.f ? -1.f : 0.f); }
 
@@ -129,6 +142,18 @@ __device__ __forceinline__ float dpp_f(float v) {
 }
 constexpr int kRowShl1 = 0x101, kRowShl2 = 0x102, kRowShl4 = 0x104, kRowShl8 = 0x108;  // lane j <- j + d
 constexpr int kRowShr1 = 0x111;                                                        // lane j <- j - 1
+
+// Sum of the lane's value over the four rows of 16 lanes (lanes j, j + 16, j +
+// 32, j + 48), in every lane: (row 0 + row 1) + (row 2 + row 3), on the
+// register swaps between rows and half waves instead of LDS shuffles.
+__device__ __forceinline__ float sum_rows(float v) {
+  const unsigned a = __float_as_uint(v);
+  const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  const float s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const unsigned b = __float_as_uint(s);
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
 
 // Float atomics with the address space stated: a generic (flat) atomic would
 // also count against the LDS wait counter, so every LDS fence after a scatter

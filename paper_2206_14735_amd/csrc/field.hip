@@ -34,33 +34,65 @@ enum : int {
   T_END = 96
 };
 
-__device__ float table_value(const float* __restrict__ P, int slot, int l) {
-  int tb, nbi;
-  if (slot < T_L2) { tb = T_L1; nbi = 1; }
-  else if (slot < T_L3) { tb = T_L2; nbi = 2; }
-  else if (slot < T_C1) { tb = T_L3; nbi = 2; }
-  else if (slot < T_C2) { tb = T_C1; nbi = 1; }
-  else if (slot < T_C2T) { tb = T_C2; nbi = 2; }
-  else if (slot < T_C1T) { tb = T_C2T; nbi = 1; }
-  else if (slot < T_L3T) { tb = T_C1T; nbi = 2; }
-  else if (slot < T_L2T) { tb = T_L3T; nbi = 1; }
-  else if (slot < T_L1T) { tb = T_L2T; nbi = 2; }
-  else { tb = T_L1T; nbi = 2; }
-  int rel = slot - tb;
-  int bo = rel / (4 * nbi), s = rel % (4 * nbi);
-  int i = 16 * bo + (l & 15);                       // output row
-  int k = 16 * (s >> 2) + 4 * (l >> 4) + (s & 3);   // input row
-  switch (tb) {
-    case T_L1: return P[oW1 + i * 16 + k];
-    case T_L2: return P[oW2 + i * 32 + k];
-    case T_L3: return P[oW3 + i * 32 + k];
-    case T_C1: return k >= 1 ? P[oU1 + i * 15 + (k - 1)] : 0.f;
-    case T_C2: return i < 3 ? P[oU2 + i * 32 + k] : 0.f;
-    case T_C2T: return k < 3 ? P[oU2 + k * 32 + i] : 0.f;
-    case T_C1T: return i >= 1 ? P[oU1 + k * 15 + (i - 1)] : 0.f;
-    case T_L3T: return P[oW3 + k * 32 + i];
-    case T_L2T: return P[oW2 + k * 32 + i];
-    default: return P[oW1 + k * 16 + i];
+// Value of lane (i, q) of slot `slot` + w, w = 0..3: every fourth slot starts a
+// group of four slots of one table (the K steps of one block pair), so its
+// table, block and steps are known at compile time: output row i + 16 bo, input
+// row 16 bi + 4 q + w.
+template <int SLOT>
+__device__ __forceinline__ float table_value(const float* __restrict__ P, int w, int i, int q) {
+  static_assert(SLOT % 4 == 0, "groups of four steps");
+  constexpr int tb = SLOT < T_L2 ? T_L1 : SLOT < T_L3 ? T_L2 : SLOT < T_C1 ? T_L3 : SLOT < T_C2 ? T_C1
+                     : SLOT < T_C2T ? T_C2 : SLOT < T_C1T ? T_C2T : SLOT < T_L3T ? T_C1T : SLOT < T_L2T ? T_L3T
+                     : SLOT < T_L1T ? T_L2T : T_L1T;
+  constexpr int nbi = (tb == T_L1 || tb == T_C1 || tb == T_C2T || tb == T_L3T) ? 1 : 2;
+  constexpr int g = (SLOT - tb) / 4, bo = g / nbi, bi = g % nbi;
+  i += 16 * bo;
+  const int k = 16 * bi + 4 * q + w;
+  if constexpr (tb == T_L1) return P[oW1 + i * 16 + k];
+  else if constexpr (tb == T_L2) return P[oW2 + i * 32 + k];
+  else if constexpr (tb == T_L3) return P[oW3 + i * 32 + k];
+  else if constexpr (tb == T_C1) return k >= 1 ? P[oU1 + i * 15 + (k - 1)] : 0.f;
+  else if constexpr (tb == T_C2) return i < 3 ? P[oU2 + i * 32 + k] : 0.f;
+  else if constexpr (tb == T_C2T) return k < 3 ? P[oU2 + k * 32 + i] : 0.f;
+  else if constexpr (tb == T_C1T) return i >= 1 ? P[oU1 + k * 15 + (i - 1)] : 0.f;
+  else if constexpr (tb == T_L3T) return P[oW3 + k * 32 + i];
+  else if constexpr (tb == T_L2T) return P[oW2 + k * 32 + i];
+  else return P[oW1 + k * 16 + i];
+}
+
+template <int SLOT, int U, int N>
+__device__ __forceinline__ void fill_load(const float* __restrict__ P, float (&v)[N], int w, int i, int q) {
+  if constexpr (U < N) {
+    v[U] = table_value<SLOT + 4 * U>(P, w, i, q);
+    fill_load<SLOT, U + 1, N>(P, v, w, i, q);
+  }
+}
+// The four steps of the groups SLOT, SLOT + 4, ... packed for the BF16 layers,
+// group SLOT / 4 + u by wave u.
+template <int SLOT>
+__device__ __forceinline__ void fill_bf16(const float* __restrict__ P, uint2* tab, int wave, int lane) {
+  if constexpr (SLOT < T_END) {
+    const int i = lane & 15, q = lane >> 4;
+    float v[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      v[w] = wave == 0 ? table_value<SLOT>(P, w, i, q) : wave == 1 ? table_value<SLOT + 4>(P, w, i, q)
+             : wave == 2 ? table_value<SLOT + 8>(P, w, i, q) : table_value<SLOT + 12>(P, w, i, q);
+    tab[(SLOT / 4 + wave) * 64 + lane] = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+    fill_bf16<SLOT + 16>(P, tab, wave, lane);
+  }
+}
+
+// Fills the FP32 tables of a block (four waves): wave w takes slot SLOT + w of
+// each group, with the loads of GROUPS groups in flight at once.
+template <int SLOT, int GROUPS>
+__device__ __forceinline__ void fill_f32(const float* __restrict__ P, float* tab, int w, int lane) {
+  if constexpr (SLOT < T_END) {
+    float v[GROUPS];
+    fill_load<SLOT, 0, GROUPS>(P, v, w, lane & 15, lane >> 4);
+#pragma unroll
+    for (int u = 0; u < GROUPS; ++u) tab[(SLOT + 4 * u + w) * 64 + lane] = v[u];
+    fill_f32<SLOT + 4 * GROUPS, GROUPS>(P, tab, w, lane);
   }
 }
 
@@ -262,11 +294,11 @@ template <bool BF, bool BWD, bool REC>
 struct FieldSmem {
   float tab[BF ? 1 : T_END * 64];
   uint2 tabbf[BF ? (T_END / 4) * 64 : 1];
-  float bias[32 + 32 + 16 + 32 + 16];   // b1, b2, b3, c1, c2(pad 16)
-  float w3row0[32];
+  alignas(16) float bias[32 + 32 + 16 + 32 + 16];   // b1, b2, b3, c1, c2(pad 16)
+  alignas(16) float w3row0[32];
   // operand transposes (2 x 32 rows), then, without records, scatter staging
   // (64 writers' 32 floats and 4 destinations)
-  float scr[kWavesPerBlock][BWD ? (REC ? 2 * 32 * RSR : 64 * 36) : 1];
+  alignas(16) float scr[kWavesPerBlock][BWD ? (REC ? 2 * 32 * RSR : 64 * 36) : 1];
 };
 constexpr int kRedFloats = kWavesPerBlock * kMlpNumel;
 // the area is reused at the end for the per-wave block partials
@@ -359,28 +391,22 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
   v4f h1[2], h2[2], ob, hc[2], cb;
   layer<BF, 2, 1>(sm, T_L1, &zb, h1, lane);
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) h1[b][r] = fmaxf(h1[b][r] + sm.bias[16 * b + 4 * q + r], 0.f);
+  for (int b = 0; b < 2; ++b) h1[b] = relu_bias(h1[b], sm.bias + 16 * b, q);
   layer<BF, 2, 2>(sm, T_L2, h1, h2, lane);
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) h2[b][r] = fmaxf(h2[b][r] + sm.bias[32 + 16 * b + 4 * q + r], 0.f);
+  for (int b = 0; b < 2; ++b) h2[b] = relu_bias(h2[b], sm.bias + 32 + 16 * b, q);
   layer<BF, 1, 2>(sm, T_L3, h2, &ob, lane);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) ob[r] += sm.bias[64 + 4 * q + r];
+  ob = plus_bias(ob, sm.bias + 64, q);
 
   // ---------------- colour decoder (ray mode)
   if (MODE == 0 && A.colour) {
     layer<BF, 2, 1>(sm, T_C1, &ob, hc, lane);
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) hc[b][r] = fmaxf(hc[b][r] + sm.bias[80 + 16 * b + 4 * q + r], 0.f);
+    for (int b = 0; b < 2; ++b) hc[b] = relu_bias(hc[b], sm.bias + 80 + 16 * b, q);
     layer<BF, 1, 2>(sm, T_C2, hc, &cb, lane);
+    cb = plus_bias(cb, sm.bias + 112, q);
 #pragma unroll
-    for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_(cb[r] + sm.bias[112 + 4 * q + r]);   // rows 0..2 of group 0 are used
+    for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_<BF>(cb[r]);   // rows 0..2 of group 0 are used
   } else {
     cb = v4f{0.f, 0.f, 0.f, 0.f};
   }
@@ -400,10 +426,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     layer<BF, 1, 2>(sm, T_L1T, e1, &ab, lane);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      float v = dot4(ab, G, a);
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
-      gx[a] = v;
+      gx[a] = sum_rows(dot4(ab, G, a));
     }
   };
   if ((!BWD || MODE == 1) && need_g) slope();
@@ -540,10 +563,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
         }
       }
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        dxv[a] += __shfl_xor(dxv[a], 16, 64);
-        dxv[a] += __shfl_xor(dxv[a], 32, 64);
-      }
+      for (int a = 0; a < 3; ++a) dxv[a] = sum_rows(dxv[a]);
       // the seeds of this sample were read at the start of the tile by this wave
       // alone; their slot takes dL/dx
       if (q == 0 && live) *reinterpret_cast<float4*>(A.grad_x + 4 * (size_t)item) = make_float4(dxv[0], dxv[1], dxv[2], 0.f);
@@ -639,25 +659,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, j = lane & 15;
 
-  if constexpr (BF) {
-    // two entries (8 loads) per thread and pass, loaded before either is stored
-    for (int e0 = tid; e0 < (T_END / 4) * 64; e0 += 2 * kBlock) {
-      float v[2][4];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int e = e0 + u * kBlock, slot = e >> 6, l = e & 63;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[u][c] = e < (T_END / 4) * 64 ? table_value(A.mlp, 4 * slot + c, l) : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int e = e0 + u * kBlock;
-        if (e < (T_END / 4) * 64) sm.tabbf[e] = make_uint2(f2bf2(v[u][0], v[u][1]), f2bf2(v[u][2], v[u][3]));
-      }
-    }
-  } else {
-    fill_batched<kBlock>(sm.tab, T_END * 64, tid, [&](int e) { return table_value(A.mlp, e >> 6, e & 63); });
-  }
+  if constexpr (BF) fill_bf16<0>(A.mlp, sm.tabbf, wave, lane);
+  else fill_f32<0, 8>(A.mlp, sm.tab, wave, lane);
   if (tid < 32) {
     sm.bias[tid] = A.mlp[oB1 + tid];
     sm.bias[32 + tid] = A.mlp[oB2 + tid];

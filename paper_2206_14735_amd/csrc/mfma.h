@@ -18,6 +18,18 @@ __device__ __forceinline__ v4s as_v4s(uint2 u) {
   return r;
 }
 
+// x + bias and relu(x + bias) of an accumulator block whose rows 4 q + r have the
+// biases bias[4 q + r] (LDS, 16-byte aligned).  The bias comes last: started
+// from it, a sum of small products would round at the bias's size at every step.
+__device__ __forceinline__ v4f plus_bias(v4f x, const float* bias, int q) {
+  const float4 b = *reinterpret_cast<const float4*>(bias + 4 * q);
+  return v4f{x[0] + b.x, x[1] + b.y, x[2] + b.z, x[3] + b.w};
+}
+__device__ __forceinline__ v4f relu_bias(v4f x, const float* bias, int q) {
+  const v4f y = plus_bias(x, bias, q);
+  return v4f{fmaxf(y[0], 0.f), fmaxf(y[1], 0.f), fmaxf(y[2], 0.f), fmaxf(y[3], 0.f)};
+}
+
 // fp32 layer: out[bo] = sum over input blocks and steps of A(slot) * in, with
 // the A operands pre-arranged per lane in `tab` (slot = base + bo*4*NBI + bi*4 + r).
 template <int NBO, int NBI>
