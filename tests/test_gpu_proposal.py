@@ -185,6 +185,37 @@ def test_proposal_driven_sampling(n_free, depth_check, extend, edge, plain_n):
     assert np.array_equal(batch.ray_of.cpu().numpy()[:seg[-1]], np.repeat(np.arange(M), lens))
 
 
+@pytest.mark.parametrize("M,plain_n,n_free", [(16384, (3, 2), None), (24577, (61, 0), None), (65539, (7, 6), None),
+                                              (16385, (16, 8), 5), (40000, (1, 0), 0), (65539, (40, 16), 5)])
+def test_rays_that_share_a_wave_are_sampled_as_alone(M, plain_n, n_free):
+    """Batches of 16384 rays and more give each wave 2 to 8 neighbouring rays;
+    a ray's samples depend on its number alone, so the batch starts with the
+    smaller batch's rays bit for bit, and (plain) ends with the oracle's."""
+    G = _G()
+    L, fr, b, grid, prop = _room(M=8, seed=7)
+    model, frd, gd, pd = G.make_model(L), fr.to("cuda"), grid.cuda(), prop.cuda()
+    got = {}
+    for m in (1999, M):
+        cfg = G.SampleCfg(m, *plain_n, G.SPAN_BOX, 0.1, 1e9, 0.1, 259, 0.004, 99, 3)
+        if n_free is not None:
+            G.set_proposal(cfg, pd, gd, n_proposal=12, conf_threshold=0.5, n_free=n_free)
+        got[m] = G.gosurf_sample_rays(model, frd, cfg)
+    torch.cuda.synchronize()
+    few, many = got[1999], got[M]
+    n = int(few.seg[1999])
+    assert torch.equal(few.seg, many.seg[:2000])
+    for k in ("o", "r", "rgb", "depth", "pixel"):
+        assert torch.equal(getattr(few, k), getattr(many, k)[:1999]), k
+    assert torch.equal(few.xs, many.xs) and torch.equal(few.eps, many.eps)
+    assert torch.equal(few.t[:n], many.t[:n]) and torch.equal(few.ray_of[:n], many.ray_of[:n])
+    seg = many.seg.cpu().numpy()
+    assert np.array_equal(many.ray_of.cpu().numpy()[:seg[-1]], np.repeat(np.arange(M), np.diff(seg)))
+    if n_free is None:
+        ref, pix, _ = osampler.sample_batch(fr, L, M, *plain_n, "aabb", 0.1, 1e9, 0.1, 0, 0.004, seed=99, step=3)
+        assert np.array_equal(seg, ref.seg) and np.array_equal(many.pixel.cpu().numpy(), pix)
+        np.testing.assert_allclose(many.t.cpu().numpy(), ref.t, rtol=4e-6, atol=1e-6)
+
+
 # Rendered-depth error of the proposal's 24 samples minus plain 96's on the
 # rays the proposal is confident about (metres).  The median and p90 stay
 # within a few millimetres; the mean carries a tail of rays whose interval
