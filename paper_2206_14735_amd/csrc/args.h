@@ -177,6 +177,32 @@ struct TargetArgs {
   float* tgt;            // [M][3]
 };
 
+// Levels whose gradient is summed in kSumRows rows of `floats` floats before it
+// joins the grid's: level l of the mask takes cnt[l] floats from off[l] on and starts at
+// row first[l] of the grid.
+constexpr int kSumRows = 64;
+struct LevelSums {
+  int floats;
+  int mask;
+  int off[4], cnt[4];
+  long long first[4];
+};
+
+// The sums that end a backward pass.
+struct GradReduceArgs {
+  const float* mlp_part;   // [rows][kMlpNumel] block partials
+  int rows;
+  float* mlp_tmp;          // [kSumRows][kMlpNumel]
+  const float* ray_dv;     // [M]
+  int M;
+  float* ray_part;         // [64][8]
+  float* grad_mlp;
+  LevelSums lev;           // floats = 0: none
+  const float* lev_part;   // [rows][floats] block partials, or nullptr if lev_tmp is there already
+  float* lev_tmp;          // [kSumRows][floats]
+  float* grad_grid;
+};
+
 struct SampleArgs {
   Grid g;
   const uint8_t* rgb;

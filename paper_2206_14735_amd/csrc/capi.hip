@@ -14,7 +14,8 @@
 namespace gs {
 
 hipError_t launch_field(const FieldArgs& a, bool bwd, int blocks, hipStream_t st);
-hipError_t launch_priv_reduce(const FieldArgs& a, int n_part, const int counts[4], float* tmp, hipStream_t st);
+LevelSums privatised_sums(const FieldArgs& a, const int counts[4]);
+LevelSums small_sums(const Grid& g, const ScatterRecords& r);
 void plan_privatised_levels(FieldArgs& a, int counts[4]);
 int priv_max_floats();
 void plan_bins(const Grid& g, Bins& b);
@@ -27,8 +28,7 @@ int field_grid(const FieldArgs& a, bool bwd);
 hipError_t launch_render(const RenderArgs& a, bool bwd, hipStream_t st);
 hipError_t launch_loss_reduce(const float* ray_partial, int M, const float* smooth_partial, int n_sp, int S,
                               const float lam[6], float* losses, float* ray_part, hipStream_t st);
-hipError_t launch_grad_reduce(const float* partial, int n_part, const float* ray_dv, int M, float* grad_mlp,
-                              float* tmp, float* ray_part, hipStream_t st);
+hipError_t launch_grad_reduce(const GradReduceArgs& a, hipStream_t st);
 hipError_t launch_adam(const gosurf_adam_cfg& c, gosurf_adam_state& s, const int* skip, hipStream_t st);
 hipError_t launch_nonfinite_check(const float* grid_grad, long long n_grid, const float* mlp_grad, long long n_mlp,
                                   int* flag, hipStream_t st);
@@ -155,7 +155,7 @@ struct Workspace {
   float* ray_dv;          // [M]
   float* mlp_partial;     // [2048][kMlpNumel]
   float* priv_partial;    // [2048][priv_max_floats]
-  float* colsum_tmp;      // [64][max(kMlpNumel, priv_max_floats)]
+  float* colsum_tmp;      // [64][kMlpNumel], then [64][priv_max_floats]
   float* ray_part;        // [64][8] block partials of sums over rays
   // scatter records (see ScatterRecords), cap = total + 2 S
   int2* place;            // [cap]
@@ -182,7 +182,7 @@ Workspace layout(char* base, int M, int total, int S) {
   w.ray_part = reinterpret_cast<float*>(take(sizeof(float) * 64 * 8));
   w.priv_partial = reinterpret_cast<float*>(take(sizeof(float) * 2048 * (size_t)gs::priv_max_floats()));
   w.colsum_tmp = reinterpret_cast<float*>(
-      take(sizeof(float) * 64 * (size_t)(gs::priv_max_floats() > gs::kMlpNumel ? gs::priv_max_floats() : gs::kMlpNumel)));
+      take(sizeof(float) * 64 * (size_t)(gs::kMlpNumel + gs::priv_max_floats())));
   w.place = reinterpret_cast<int2*>(take(sizeof(int2) * cap));
   w.tables = reinterpret_cast<float*>(take(sizeof(float) * (size_t)gs::max_tables()));
   w.bin_first = reinterpret_cast<unsigned*>(take(sizeof(unsigned) * gs::kMaxBins));
@@ -590,17 +590,17 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
     if ((st = hip_check(gs::launch_scatter(sa, s), "grid scatter")) != GOSURF_OK) return st;
   }
   mark(GOSURF_KERNEL_FIELD_BWD, false, s);
-  if (!records &&
-      (st = hip_check(gs::launch_priv_reduce(fa, nb, counts, w.colsum_tmp, s), "level reduce")) != GOSURF_OK)
-    return st;
   if (ray_grads &&
       (st = hip_check(gs::launch_ray_xgrad(w.seed4, b->t, b->seg, b->M, b->total, grads->ray_o, grads->ray_r, s),
                       "ray gradients")) != GOSURF_OK)
     return st;
-  if ((st = hip_check(gs::launch_grad_reduce(w.mlp_partial, nb, w.ray_dv, b->M, grads->mlp, w.colsum_tmp,
-                                             w.ray_part, s),
-                      "grad reduce")) != GOSURF_OK)
-    return st;
+  gs::GradReduceArgs gr{};
+  gr.mlp_part = w.mlp_partial; gr.rows = nb; gr.mlp_tmp = w.colsum_tmp; gr.ray_dv = w.ray_dv; gr.M = b->M;
+  gr.ray_part = w.ray_part; gr.grad_mlp = grads->mlp; gr.grad_grid = grads->grid;
+  gr.lev = records ? gs::small_sums(g, rec) : gs::privatised_sums(fa, counts);
+  gr.lev_part = records ? nullptr : w.priv_partial;
+  gr.lev_tmp = records ? rec.small : w.colsum_tmp + 64 * (size_t)gs::kMlpNumel;
+  if ((st = hip_check(gs::launch_grad_reduce(gr, s), "grad reduce")) != GOSURF_OK) return st;
   if (cgrid) {
     // the colour path: its own kernel on the colour seeds; its decoder partials
     // reuse the decoder-partial rows, whose reduction above is already enqueued

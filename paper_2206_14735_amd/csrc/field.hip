@@ -782,45 +782,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !
   }
 }
 
-
-
-// sum of the block partials of the privatised levels into the grid gradient
-// (one writer per entry, fixed block order)
-struct PrivMap {
-  int mask;
-  int po[4], pc[4];
-  long long go[4];
-};
-
-__global__ __launch_bounds__(256) void priv_stage2_kernel(const float* __restrict__ tmp, int floats, PrivMap pm,
-                                                          float* __restrict__ grad) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= floats) return;
-  float s = 0.f;
-#pragma unroll 8
-  for (int y = 0; y < 64; ++y) s += tmp[(size_t)y * floats + e];
-  for (int l = 0; l < 4; ++l)
-    if (((pm.mask >> l) & 1) && e >= pm.po[l] && e < pm.po[l] + pm.pc[l]) grad[pm.go[l] * 4 + (e - pm.po[l])] += s;
-}
-
-hipError_t launch_colsum_stage1(const float* part, int rows, int cols, float* tmp, hipStream_t st);
-int colsum_rows();
-
-hipError_t launch_priv_reduce(const FieldArgs& a, int n_part, const int counts[4], float* tmp, hipStream_t st) {
-  if (a.priv_floats <= 0) return hipSuccess;
-  if (colsum_rows() != 64) return hipErrorInvalidValue;
-  PrivMap pm;
-  pm.mask = a.priv_mask;
+// The levels summed in LDS, as rows of block partials for the sums that end the
+// pass.
+LevelSums privatised_sums(const FieldArgs& a, const int counts[4]) {
+  LevelSums m;
+  m.floats = a.priv_floats;
+  m.mask = a.priv_mask;
   for (int l = 0; l < 4; ++l) {
-    pm.po[l] = a.priv_off[l];
-    pm.pc[l] = counts[l];
-    pm.go[l] = a.g.off[l];
+    m.off[l] = a.priv_off[l];
+    m.cnt[l] = counts[l];
+    m.first[l] = a.g.off[l];
   }
-  hipError_t e = launch_colsum_stage1(a.priv_partial, n_part, a.priv_floats, tmp, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(priv_stage2_kernel, dim3((a.priv_floats + 255) / 256), dim3(256), 0, st, tmp, a.priv_floats,
-                     pm, a.grad_grid);
-  return hipGetLastError();
+  return m;
 }
 
 void plan_privatised_levels(FieldArgs& a, int counts[4]) {

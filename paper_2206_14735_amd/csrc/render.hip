@@ -505,13 +505,13 @@ __global__ __launch_bounds__(256) void render_bwd_kernel(RenderArgs A) {
 // over its 256 threads in a fixed tree, into part[b][0..NCOL-1] (rows of 8).
 constexpr int kRaySumBlocks = 64;
 template <int NCOL>
-__global__ __launch_bounds__(256) void ray_sum_stage1_kernel(const float* __restrict__ x, int M, int stride,
-                                                             float* __restrict__ part) {
+__device__ __forceinline__ void ray_sum_stage1(const float* __restrict__ x, int M, int stride,
+                                               float* __restrict__ part, int block, int blocks) {
   __shared__ float red[NCOL][256];
   float acc[NCOL];
 #pragma unroll
   for (int c = 0; c < NCOL; ++c) acc[c] = 0.f;
-  for (int m = blockIdx.x * 256 + threadIdx.x; m < M; m += gridDim.x * 256)
+  for (int m = block * 256 + threadIdx.x; m < M; m += blocks * 256)
 #pragma unroll
     for (int c = 0; c < NCOL; ++c) acc[c] += x[(size_t)m * stride + c];
 #pragma unroll
@@ -523,21 +523,69 @@ __global__ __launch_bounds__(256) void ray_sum_stage1_kernel(const float* __rest
       for (int c = 0; c < NCOL; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x < NCOL) part[8 * blockIdx.x + threadIdx.x] = red[threadIdx.x][0];
+  if (threadIdx.x < NCOL) part[8 * block + threadIdx.x] = red[threadIdx.x][0];
 }
 
-int ray_sum_blocks(int M) {
+__global__ __launch_bounds__(256) void loss_stage1_kernel(const float* __restrict__ x, int M, float* __restrict__ part) {
+  ray_sum_stage1<6>(x, M, 8, part, blockIdx.x, gridDim.x);
+}
+
+__host__ __device__ inline int ray_sum_blocks(int M) {
   const int b = (M + 255) / 256;
   return b < 1 ? 1 : (b > kRaySumBlocks ? kRaySumBlocks : b);
 }
 
-// Stage 2 of the loss: the block partials of the six per-ray columns (rgb,
-// depth, sdf, fs, eik, rays with depth) in block order, the smoothness block
-// partials in a fixed tree; then the set means and the weighted total.
+// The losses of the six per-ray sums (rgb, depth, sdf, fs, eik, rays with depth)
+// and the smoothness sum: set means and the weighted total.
+struct LossCoef {
+  float lam[6];
+};
+__device__ __forceinline__ void write_losses(const float col[6], float smooth, int M, int S, const LossCoef& k,
+                                             float* __restrict__ losses) {
+  const float invM = 1.f / (float)M;
+  const float nd = col[5];
+  const float L[6] = {col[0] * invM, nd > 0.f ? col[1] / nd : 0.f, col[2] * invM,
+                      col[3] * invM, col[4] * invM, S > 0 ? smooth / (float)S : 0.f};
+  float tot = 0.f;
+#pragma unroll
+  for (int c = 0; c < 6; ++c) { losses[c] = L[c]; tot += k.lam[c] * L[c]; }
+  losses[6] = tot;
+  losses[7] = nd;
+}
+
+// The losses of at most kLossRays rays in one block: its 1024 threads read the
+// rays' terms in at most 8 turns (6144 rays: 5.0 us, 9.2 us in the two launches
+// below; 509 rays: 3.1 and 5.3 us).  Beyond, one block's loads take longer than
+// a second launch.
+constexpr int kLossRays = 8192;
+__global__ __launch_bounds__(1024) void loss_kernel(const float* __restrict__ x, int M,
+                                                    const float* __restrict__ smooth_partial, int n_sp, int S,
+                                                    LossCoef k, float* __restrict__ losses) {
+  __shared__ float red[16][8];
+  float acc[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int m = threadIdx.x; m < M; m += 1024)
+#pragma unroll
+    for (int c = 0; c < 6; ++c) acc[c] += x[(size_t)m * 8 + c];
+  for (int i = threadIdx.x; i < n_sp; i += 1024) acc[6] += smooth_partial[i];
+#pragma unroll
+  for (int c = 0; c < 7; ++c) {
+    const float s = wave_sum_dpp(acc[c]);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][c] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  float col[7];
+#pragma unroll
+  for (int c = 0; c < 7; ++c) col[c] = wave_sum_dpp(threadIdx.x < 16 ? red[threadIdx.x][c] : 0.f);
+  if (threadIdx.x == 0) write_losses(col, col[6], M, S, k, losses);
+}
+
+// Stage 2 of the loss: the block partials of the six per-ray columns in block
+// order, the smoothness block partials in a fixed tree.
 __global__ __launch_bounds__(256) void loss_final_kernel(const float* __restrict__ part, int nb,
                                                          const float* __restrict__ smooth_partial, int n_sp, int M,
-                                                         int S, float l0, float l1, float l2, float l3, float l4,
-                                                         float l5, float* __restrict__ losses) {
+                                                         int S, LossCoef k, float* __restrict__ losses) {
   __shared__ float sred[256];
   float sm = 0.f;
   for (int i = threadIdx.x; i < n_sp; i += 256) sm += smooth_partial[i];
@@ -554,28 +602,16 @@ __global__ __launch_bounds__(256) void loss_final_kernel(const float* __restrict
 #pragma unroll
     for (int c = 0; c < 6; ++c) col[c] = wave_sum_dpp((int)threadIdx.x < nb ? part[8 * threadIdx.x + c] : 0.f);
   }
-  if (threadIdx.x == 0) {
-    const float invM = 1.f / (float)M;
-    const float nd = col[5];
-    const float L[6] = {col[0] * invM, nd > 0.f ? col[1] / nd : 0.f, col[2] * invM,
-                        col[3] * invM, col[4] * invM, S > 0 ? sred[0] / (float)S : 0.f};
-    const float lam[6] = {l0, l1, l2, l3, l4, l5};
-    float tot = 0.f;
-    for (int k = 0; k < 6; ++k) { losses[k] = L[k]; tot += lam[k] * L[k]; }
-    losses[6] = tot;
-    losses[7] = nd;
-  }
+  if (threadIdx.x == 0) write_losses(col, sred[0], M, S, k, losses);
 }
 
 // Column sums of a [rows][cols] matrix of block partials, in two fixed-order
 // stages: block (x, y) sums rows y, y + R1, y + 2 R1, ... of columns
 // 256x .. 256x + 255 into tmp[y][col]; the second stage sums the R1 rows of tmp.
-constexpr int kR1 = 64;
+constexpr int kR1 = kSumRows;
 
-__global__ __launch_bounds__(256) void colsum_stage1_kernel(const float* __restrict__ part, int rows, int cols,
-                                                            float* __restrict__ tmp) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int y = blockIdx.y;
+__device__ __forceinline__ void colsum_stage1(const float* __restrict__ part, int rows, int cols, int e, int y,
+                                              float* __restrict__ tmp) {
   if (e >= cols) return;
   float s0 = 0.f, s1 = 0.f;
   int r = y;
@@ -594,37 +630,57 @@ __device__ __forceinline__ float colsum_stage2(const float* __restrict__ tmp, in
   return s;
 }
 
-// grads.mlp += column sums; entry v gets the per-ray dL/dv sums instead (the
-// nb block partials of ray_sum_stage1, in block order)
-__global__ __launch_bounds__(256) void grad_stage2_kernel(const float* __restrict__ tmp, const float* __restrict__ dv_part,
-                                                          int nb, float* __restrict__ grad_mlp) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= kMlpNumel) return;
-  if (blockIdx.x == 0 && threadIdx.x < 64) {   // wave 0 of block 0: the nb <= 64 dL/dv partials
-    const float s = wave_sum_dpp((int)threadIdx.x < nb ? dv_part[8 * threadIdx.x] : 0.f);
-    if (threadIdx.x == 0) grad_mlp[oV] += s;
+__global__ __launch_bounds__(256) void colsum_stage1_kernel(const float* __restrict__ part, int rows, int cols,
+                                                            float* __restrict__ tmp) {
+  colsum_stage1(part, rows, cols, blockIdx.x * 256 + threadIdx.x, blockIdx.y, tmp);
+}
+
+// The backward's last sums, each in two fixed-order stages: the decoder's block
+// partials, the levels summed apart from the grid and the per-ray dL/dv.  Each
+// stage is one launch whose blocks share out the three (stage 1: kR1 rows of
+// col_blocks blocks, the first mlp_blocks of them the decoder's, then the rays').
+// Five launches of about 4.7 us each on a 6144-ray batch before.
+__global__ __launch_bounds__(256) void grad_stage1_kernel(GradReduceArgs A, int mlp_blocks, int col_blocks) {
+  const int b = blockIdx.x;
+  if (b >= kR1 * col_blocks) {
+    ray_sum_stage1<1>(A.ray_dv, A.M, 1, A.ray_part, b - kR1 * col_blocks, ray_sum_blocks(A.M));
+    return;
   }
-  if (e == oV) return;
-  grad_mlp[e] += colsum_stage2(tmp, kMlpNumel, e);
+  const int y = b / col_blocks, bx = b - y * col_blocks;
+  if (bx < mlp_blocks) colsum_stage1(A.mlp_part, A.rows, kMlpNumel, bx * 256 + threadIdx.x, y, A.mlp_tmp);
+  else colsum_stage1(A.lev_part, A.rows, A.lev.floats, (bx - mlp_blocks) * 256 + threadIdx.x, y, A.lev_tmp);
 }
 
-hipError_t launch_colsum_stage1(const float* part, int rows, int cols, float* tmp, hipStream_t st) {
-  hipLaunchKernelGGL(colsum_stage1_kernel, dim3((cols + 255) / 256, kR1), dim3(256), 0, st, part, rows, cols, tmp);
+// grads.mlp += column sums; entry v gets the per-ray dL/dv sums instead (the
+// block partials of stage 1, in block order); the levels' sums join the grid's.
+__global__ __launch_bounds__(256) void grad_stage2_kernel(GradReduceArgs A, int mlp_blocks) {
+  if ((int)blockIdx.x >= mlp_blocks) {
+    const int e = ((int)blockIdx.x - mlp_blocks) * 256 + threadIdx.x;
+    if (e >= A.lev.floats) return;
+    const float s = colsum_stage2(A.lev_tmp, A.lev.floats, e);
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      const int at = e - A.lev.off[l];
+      if (((A.lev.mask >> l) & 1) && at >= 0 && at < A.lev.cnt[l]) A.grad_grid[4 * A.lev.first[l] + at] += s;
+    }
+    return;
+  }
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {   // wave 0 of block 0: the at most 64 dL/dv partials
+    const float s = wave_sum_dpp((int)threadIdx.x < ray_sum_blocks(A.M) ? A.ray_part[8 * threadIdx.x] : 0.f);
+    if (threadIdx.x == 0) A.grad_mlp[oV] += s;
+  }
+  if (e >= kMlpNumel || e == oV) return;
+  A.grad_mlp[e] += colsum_stage2(A.mlp_tmp, kMlpNumel, e);
+}
+
+hipError_t launch_grad_reduce(const GradReduceArgs& a, hipStream_t st) {
+  const int mb = (kMlpNumel + 255) / 256, lb = (a.lev.floats + 255) / 256, nb = ray_sum_blocks(a.M);
+  const int cb = mb + (a.lev_part ? lb : 0);
+  hipLaunchKernelGGL(grad_stage1_kernel, dim3(kR1 * cb + nb), dim3(256), 0, st, a, mb, cb);
+  hipLaunchKernelGGL(grad_stage2_kernel, dim3(mb + lb), dim3(256), 0, st, a, mb);
   return hipGetLastError();
 }
-
-hipError_t launch_grad_reduce(const float* partial, int n_part, const float* ray_dv, int M, float* grad_mlp,
-                              float* tmp, float* ray_part, hipStream_t st) {
-  hipError_t e = launch_colsum_stage1(partial, n_part, kMlpNumel, tmp, st);
-  if (e != hipSuccess) return e;
-  const int nb = ray_sum_blocks(M);
-  hipLaunchKernelGGL(ray_sum_stage1_kernel<1>, dim3(nb), dim3(256), 0, st, ray_dv, M, 1, ray_part);
-  hipLaunchKernelGGL(grad_stage2_kernel, dim3((kMlpNumel + 255) / 256), dim3(256), 0, st, tmp, ray_part, nb,
-                     grad_mlp);
-  return hipGetLastError();
-}
-
-int colsum_rows() { return kR1; }
 
 // dst[e] += column sum e for e < n_add; set_dst = column sum `set_col`
 __global__ __launch_bounds__(256) void colsum_stage2_kernel(const float* __restrict__ tmp, int cols,
@@ -639,8 +695,7 @@ __global__ __launch_bounds__(256) void colsum_stage2_kernel(const float* __restr
 
 hipError_t launch_colsum(const float* part, int rows, int cols, float* tmp, float* add_dst, int n_add,
                          float* set_dst, int set_col, hipStream_t st) {
-  hipError_t e = launch_colsum_stage1(part, rows, cols, tmp, st);
-  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(colsum_stage1_kernel, dim3((cols + 255) / 256, kR1), dim3(256), 0, st, part, rows, cols, tmp);
   hipLaunchKernelGGL(colsum_stage2_kernel, dim3((cols + 255) / 256), dim3(256), 0, st, tmp, cols, add_dst, n_add,
                      set_dst, set_col);
   return hipGetLastError();
@@ -739,10 +794,15 @@ hipError_t launch_render(const RenderArgs& a, bool bwd, hipStream_t st) {
 
 hipError_t launch_loss_reduce(const float* ray_partial, int M, const float* smooth_partial, int n_sp, int S,
                               const float lam[6], float* losses, float* ray_part, hipStream_t st) {
+  LossCoef k;
+  for (int c = 0; c < 6; ++c) k.lam[c] = lam[c];
+  if (M <= kLossRays) {
+    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(1024), 0, st, ray_partial, M, smooth_partial, n_sp, S, k, losses);
+    return hipGetLastError();
+  }
   const int nb = ray_sum_blocks(M);
-  hipLaunchKernelGGL(ray_sum_stage1_kernel<6>, dim3(nb), dim3(256), 0, st, ray_partial, M, 8, ray_part);
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, ray_part, nb, smooth_partial, n_sp, M, S, lam[0],
-                     lam[1], lam[2], lam[3], lam[4], lam[5], losses);
+  hipLaunchKernelGGL(loss_stage1_kernel, dim3(nb), dim3(256), 0, st, ray_partial, M, ray_part);
+  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, ray_part, nb, smooth_partial, n_sp, M, S, k, losses);
   return hipGetLastError();
 }
 

@@ -460,20 +460,18 @@ __global__ __launch_bounds__(64) void scatter_kernel(ScatterArgs A, int chunk) {
   if (cur >= 0) flush_window(wl, reinterpret_cast<float*>(win), verts, cur, nbx, nby, lane);
 }
 
-// grad += the small levels' copies, in order
-__global__ __launch_bounds__(256) void small_fold_kernel(ScatterArgs A) {
-  const ScatterRecords& R = A.rec;
-  const int e = blockIdx.x * 256 + threadIdx.x, n = 4 * R.small_verts;
-  if (e >= n) return;
-  float s = 0.f;
-#pragma unroll 16
-  for (int c = 0; c < kSmallCopies; ++c) s += R.small[(size_t)c * n + e];
-#pragma unroll
+// The small levels' copies as rows for the sums that end the pass.
+static_assert(kSmallCopies == kSumRows, "the copies are the rows of the sums");
+LevelSums small_sums(const Grid& g, const ScatterRecords& r) {
+  LevelSums m;
+  m.floats = 4 * r.small_verts;
+  m.mask = r.small_mask;
   for (int l = 0; l < 4; ++l) {
-    const int at = e - 4 * R.small_off[l];
-    if (((R.small_mask >> l) & 1) && at >= 0 && at < 4 * A.g.nx[l] * A.g.ny[l] * A.g.nz[l])
-      A.grad_grid[4 * A.g.off[l] + at] += s;
+    m.off[l] = 4 * r.small_off[l];
+    m.cnt[l] = (r.small_mask >> l) & 1 ? 4 * g.nx[l] * g.ny[l] * g.nz[l] : 0;
+    m.first[l] = g.off[l];
   }
+  return m;
 }
 
 hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st) {
@@ -498,8 +496,6 @@ hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st) {
   if (blocks > waves) blocks = waves;   // a multiple of kQueues, as drawing needs
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)chunk);
-  if (a.rec.small_verts > 0)
-    hipLaunchKernelGGL(small_fold_kernel, dim3((4 * a.rec.small_verts + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

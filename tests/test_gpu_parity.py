@@ -498,3 +498,31 @@ def test_record_scatter_matches_oracle(grid):
     b = _clear(grid_, mlp, L, b)
     assert bins <= 256 and len(b.t) + 2 * len(b.xs) >= 512 * bins
     compare(run_device(L, b, grid_, mlp), *oracle_pair(grid_, mlp, L, b), case=(L, b, mlp))
+
+
+@pytest.mark.parametrize("M", [1, 63, 1025, 8192, 8193, 20000])
+def test_losses_are_the_sums_of_their_terms(M):
+    """Batches of up to 8192 rays are summed by one block, larger ones in two
+    stages.  The terms are not negative and a sum passes through at most 8 + 24
+    float32 additions per term, so each loss is within 32 * 2^-24 of the exact
+    sum of the float32 terms, and the quotients add two roundings."""
+    G = _G()
+    w = synth.configs.SPHERE
+    L = f32_layout(w.layout())
+    S = 777
+    cfg = G.SampleCfg(M, 5, 4, G.SPAN_BOX, 0.1, 3.0, 0.1, S, 0.004, 5, 0)
+    model = G.make_model(L)
+    db = G.gosurf_sample_rays(model, synth.sphere_frames().to("cuda"), cfg)
+    grid, mlp = synth.init_params(L, seed=5, grid_std=0.01)
+    out = G.FwdOut.empty(M, db.total, "cuda", terms_S=S)
+    G.gosurf_forward(model, grid.cuda().contiguous(), mlp.cuda().contiguous(), db, G.make_loss_cfg(LAMBDAS),
+                     G.workspace_for(model, M, db.total, S), out=out)
+    torch.cuda.synchronize()
+    t = out.ray_terms.double().sum(0).cpu().numpy()
+    nd = t[5]
+    exact = [t[0] / M, t[1] / nd if nd > 0 else 0.0, t[2] / M, t[3] / M, t[4] / M,
+             float(out.pair_terms.double().sum()) / S]
+    got = out.losses.cpu().double().numpy()
+    assert got[7] == nd
+    np.testing.assert_allclose(got[:6], exact, rtol=34 * 2.0 ** -24, atol=1e-30)
+    np.testing.assert_allclose(got[6], np.dot(LAMBDAS, exact), rtol=40 * 2.0 ** -24)
