@@ -245,8 +245,7 @@ struct ImpArgs {
   const float* o;
   const float* r;
   const float* t;        // [M][n] sorted
-  const float* phi;      // SDF of sample i at phi[i * phi_stride]
-  int phi_stride;
+  const float* phi;      // SDF of the samples
   const float* mlp;      // sharpness s = exp(10 v)
   int M, n, n_add;
   float eps;             // added to every interval weight
@@ -256,11 +255,11 @@ struct ImpArgs {
 };
 struct ImpMergeArgs {
   const float* ta;       // [M][na] sorted
-  const float* pa;       // value carried with ta: pa[i * pa_stride]
-  int pa_stride, na;
+  const float* pa;       // value carried with ta
+  int na;
   const float* tb;       // [M][nb]
   const float* pb;
-  int pb_stride, nb;
+  int nb;
   int M;
   float* t_out;          // [M][na + nb]
   float* p_out;          // or null
@@ -270,14 +269,22 @@ struct ImpMergeArgs {
 
 // Surface extraction: lattice rows as rays for the forward field kernel, and
 // marching tetrahedra over the SDF lattice.
-struct LatticeArgs {
+// SDF alone, of ray samples (t, ray_of) or, without them, of lattice points
+// p0 + h (i, j, k), x fastest, z layers from k0 on.
+struct PhiArgs {
+  Grid g;
+  const float* grid;
+  const uint16_t* grid_bf16;
+  const float* mlp;
+  const float* o;
+  const float* r;
+  const float* t;
+  const int* ray_of;
+  int total;
+  float* phi;               // [total]
   float p0[3];
   float h;
-  int nx, ny, k0, layers;   // a slab of `layers` z-layers starting at k0
-  float* t;                 // [nx * ny * layers]
-  int* ray_of;              // [nx * ny * layers]
-  float* o;                 // [ny * layers][3]
-  float* r;                 // [ny * layers][3]
+  int nx, ny, k0;
 };
 struct MtArgs {
   const float* phi;         // [nz][ny][nx]

@@ -47,8 +47,7 @@ hipError_t launch_colsum(const float* part, int rows, int cols, float* tmp, floa
                          float* set_dst, int set_col, hipStream_t st);
 hipError_t launch_importance_step(const ImpArgs& a, hipStream_t st);
 hipError_t launch_importance_merge(const ImpMergeArgs& a, hipStream_t st);
-hipError_t launch_lattice_rays(const LatticeArgs& a, hipStream_t st);
-hipError_t launch_phi_copy(const float* out4, long long n, float* phi, hipStream_t st);
+hipError_t launch_phi(const PhiArgs& a, hipStream_t st);
 hipError_t launch_marching_tets(const MtArgs& a, hipStream_t st);
 hipError_t launch_pose_apply(const float* c2w0, const float* pose, int T, float* c2w, hipStream_t st);
 hipError_t launch_colour(const ColourArgs& a, bool bwd, int blocks, hipStream_t st);
@@ -823,8 +822,8 @@ struct ImpWorkspace {
   float* pb;
   float* t_new;     // [M][n_add]
   int* ray_new;     // [M][n_add]
-  float* out_c;     // [M][n0][4] forward outputs at the coarse samples
-  float* out_n;     // [M][n_add][4] forward outputs at the new samples
+  float* out_c;     // [M][n0] SDF at the coarse samples
+  float* out_n;     // [M][n_add] SDF at the new samples
   size_t bytes;
 };
 
@@ -839,23 +838,26 @@ ImpWorkspace imp_layout(char* base, int M, int n0, int n_add, int steps) {
   w.pb = reinterpret_cast<float*>(take(sizeof(float) * M * nf));
   w.t_new = reinterpret_cast<float*>(take(sizeof(float) * M * (size_t)n_add));
   w.ray_new = reinterpret_cast<int*>(take(sizeof(int) * M * (size_t)n_add));
-  w.out_c = reinterpret_cast<float*>(take(sizeof(float) * 4 * M * (size_t)n0));
-  w.out_n = reinterpret_cast<float*>(take(sizeof(float) * 4 * M * (size_t)n_add));
+  w.out_c = reinterpret_cast<float*>(take(sizeof(float) * M * (size_t)n0));
+  w.out_n = reinterpret_cast<float*>(take(sizeof(float) * M * (size_t)n_add));
   w.bytes = off;
   return w;
 }
 
-// SDF (with colour) of `total` samples given by (t, ray_of) through the forward field kernel
+gs::PhiArgs phi_args(const gosurf_model* model, const gosurf_params* params, int total, float* phi) {
+  gs::PhiArgs a{};
+  a.g = to_grid(model); a.grid = params->grid; a.mlp = params->mlp;
+  a.grid_bf16 = model->precision == GOSURF_BF16 ? params->grid_bf16 : nullptr;
+  a.total = total; a.phi = phi;
+  return a;
+}
+
+// SDF of `total` samples given by (t, ray_of)
 gosurf_status field_phi(const gosurf_model* model, const gosurf_params* params, const gosurf_ray_batch* rays,
-                        const float* t, const int* ray_of, int total, float* out4, hipStream_t s) {
-  gs::FieldArgs fa{};
-  fa.g = to_grid(model); fa.grid = params->grid; fa.mlp = params->mlp;
-  fa.grid_bf16 = model->precision == GOSURF_BF16 ? params->grid_bf16 : nullptr;
-  fa.o = rays->o; fa.r = rays->r; fa.t = t; fa.ray_of = ray_of; fa.total = total;
-  fa.S = 0; fa.out4 = out4; fa.need_gx = 0;
-  const int nb = gs::field_grid(fa, false);
-  if (nb <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
-  return hip_check(gs::launch_field(fa, false, nb, s), "field fwd (importance)");
+                        const float* t, const int* ray_of, int total, float* phi, hipStream_t s) {
+  gs::PhiArgs a = phi_args(model, params, total, phi);
+  a.o = rays->o; a.r = rays->r; a.t = t; a.ray_of = ray_of;
+  return hip_check(gs::launch_phi(a, s), "SDF of the samples");
 }
 
 }  // namespace
@@ -882,7 +884,7 @@ gosurf_status gosurf_importance_step(const gosurf_model* model, const float* mlp
     return fail(GOSURF_ERR_SHAPE, "%d samples per ray (2..%d)", n, GOSURF_MAX_SAMPLES_PER_RAY);
   if (step_index < 0) return fail(GOSURF_ERR_VALUE, "step_index = %d < 0", step_index);
   gs::ImpArgs a{};
-  a.g = to_grid(model); a.o = rays->o; a.r = rays->r; a.t = rays->t; a.phi = phi; a.phi_stride = 1;
+  a.g = to_grid(model); a.o = rays->o; a.r = rays->r; a.t = rays->t; a.phi = phi;
   a.mlp = mlp; a.M = rays->M; a.n = n; a.n_add = cfg->n_add; a.eps = cfg->weight_eps;
   a.k0 = (uint32_t)(cfg->seed & 0xffffffffu); a.k1 = (uint32_t)(cfg->seed >> 32);
   a.iteration = (uint32_t)cfg->step; a.stream = kImpStream + (uint32_t)step_index;
@@ -922,12 +924,12 @@ gosurf_status gosurf_importance_sample(const gosurf_model* model, const gosurf_p
     return st;
   const float* t_cur = coarse->t;
   const float* p_cur = w.out_c;
-  int p_stride = 4, n = n0;
+  int n = n0;
   float* t_dst = w.tb;
   float* p_dst = w.pb;
   for (int k = 0; k < cfg->steps; ++k) {
     gs::ImpArgs a{};
-    a.g = to_grid(model); a.o = coarse->o; a.r = coarse->r; a.t = t_cur; a.phi = p_cur; a.phi_stride = p_stride;
+    a.g = to_grid(model); a.o = coarse->o; a.r = coarse->r; a.t = t_cur; a.phi = p_cur;
     a.mlp = params->mlp; a.M = M; a.n = n; a.n_add = cfg->n_add; a.eps = cfg->weight_eps;
     a.k0 = (uint32_t)(cfg->seed & 0xffffffffu); a.k1 = (uint32_t)(cfg->seed >> 32);
     a.iteration = (uint32_t)cfg->step; a.stream = kImpStream + (uint32_t)k;
@@ -937,14 +939,14 @@ gosurf_status gosurf_importance_sample(const gosurf_model* model, const gosurf_p
       return st;
     const bool last = k + 1 == cfg->steps;
     gs::ImpMergeArgs mg{};
-    mg.ta = t_cur; mg.pa = p_cur; mg.pa_stride = p_stride; mg.na = n;
-    mg.tb = w.t_new; mg.pb = w.out_n; mg.pb_stride = 4; mg.nb = cfg->n_add; mg.M = M;
+    mg.ta = t_cur; mg.pa = p_cur; mg.na = n;
+    mg.tb = w.t_new; mg.pb = w.out_n; mg.nb = cfg->n_add; mg.M = M;
     mg.t_out = last ? out->t : t_dst;
     mg.p_out = last ? nullptr : p_dst;
     mg.ray_of_out = last ? out->ray_of : nullptr;
     mg.seg_out = last ? out->seg : nullptr;
     if ((st = hip_check(gs::launch_importance_merge(mg, s), "importance merge")) != GOSURF_OK) return st;
-    t_cur = t_dst; p_cur = p_dst; p_stride = 1; n += cfg->n_add;
+    t_cur = t_dst; p_cur = p_dst; n += cfg->n_add;
     t_dst = (t_dst == w.tb) ? w.ta : w.tb;
     p_dst = (p_dst == w.pb) ? w.pa : w.pb;
   }
@@ -956,27 +958,12 @@ gosurf_status gosurf_importance_sample(const gosurf_model* model, const gosurf_p
 // ---------------------------------------------------------------- surface extraction
 namespace {
 
-struct LatWorkspace {
-  float* t;
-  int* ray_of;
-  float* out4;
-  float* o;
-  float* r;
-  size_t bytes;
-};
-
-LatWorkspace lat_layout(char* base, long long nx, long long ny, long long layers) {
-  LatWorkspace w{};
-  size_t off = 0;
+// Bytes asked of a caller for `layers` z-layers.  The lattice needs no scratch;
+// the size is that of the rays and outputs of its rows, which earlier versions
+// kept there, and a smaller workspace is refused as before.
+size_t lat_bytes(long long nx, long long ny, long long layers) {
   const size_t n = (size_t)(nx * ny * layers), rows = (size_t)(ny * layers);
-  auto take = [&](size_t b) { char* p = base ? base + off : nullptr; off += up(b); return p; };
-  w.t = reinterpret_cast<float*>(take(sizeof(float) * n));
-  w.ray_of = reinterpret_cast<int*>(take(sizeof(int) * n));
-  w.out4 = reinterpret_cast<float*>(take(sizeof(float) * 4 * n));
-  w.o = reinterpret_cast<float*>(take(sizeof(float) * 3 * rows));
-  w.r = reinterpret_cast<float*>(take(sizeof(float) * 3 * rows));
-  w.bytes = off;
-  return w;
+  return 2 * up(sizeof(float) * n) + up(sizeof(float) * 4 * n) + 2 * up(sizeof(float) * 3 * rows);
 }
 
 gosurf_status check_lattice(const float* p0, float h, int nx, int ny, int nz) {
@@ -994,7 +981,7 @@ extern "C" {
 
 size_t gosurf_lattice_workspace_bytes(int32_t nx, int32_t ny, int32_t layers) {
   if (nx < 1 || ny < 1 || layers < 1) return 0;
-  return lat_layout(nullptr, nx, ny, layers).bytes;
+  return lat_bytes(nx, ny, layers);
 }
 
 gosurf_status gosurf_sdf_lattice(const gosurf_model* model, const gosurf_params* params, const float p0[3],
@@ -1005,40 +992,18 @@ gosurf_status gosurf_sdf_lattice(const gosurf_model* model, const gosurf_params*
   if ((st = check_params(model, params)) != GOSURF_OK) return st;
   if ((st = check_lattice(p0, h, nx, ny, nz)) != GOSURF_OK) return st;
   if (!phi || !ws) return fail(GOSURF_ERR_NULL, "phi or the workspace is NULL");
-  // the largest slab that fits the workspace and the field kernel's sample indexing
-  long long layers = 0;
-  for (long long lo = 1, hi = nz; lo <= hi;) {
-    const long long mid = (lo + hi) / 2;
-    if (lat_layout(nullptr, nx, ny, mid).bytes <= ws_bytes && (long long)nx * ny * mid * 4 < (1LL << 31)) {
-      layers = mid;
-      lo = mid + 1;
-    } else {
-      hi = mid - 1;
-    }
-  }
-  if (layers < 1)
+  if (lat_bytes(nx, ny, 1) > ws_bytes)
     return fail(GOSURF_ERR_WORKSPACE, "workspace of %zu bytes holds no z-layer (%zu needed)", ws_bytes,
-                lat_layout(nullptr, nx, ny, 1).bytes);
-  const LatWorkspace w = lat_layout(static_cast<char*>(ws), nx, ny, layers);
-  hipStream_t s = (hipStream_t)stream;
-  for (int k0 = 0; k0 < nz; k0 += (int)layers) {
-    const int L = (int)((nz - k0) < layers ? (nz - k0) : layers);
-    gs::LatticeArgs la{};
-    for (int a = 0; a < 3; ++a) la.p0[a] = p0[a];
-    la.h = h; la.nx = nx; la.ny = ny; la.k0 = k0; la.layers = L;
-    la.t = w.t; la.ray_of = w.ray_of; la.o = w.o; la.r = w.r;
-    if ((st = hip_check(gs::launch_lattice_rays(la, s), "lattice rays")) != GOSURF_OK) return st;
-    gs::FieldArgs fa{};
-    fa.g = to_grid(model); fa.grid = params->grid; fa.mlp = params->mlp;
-    fa.grid_bf16 = model->precision == GOSURF_BF16 ? params->grid_bf16 : nullptr;
-    fa.o = w.o; fa.r = w.r; fa.t = w.t; fa.ray_of = w.ray_of; fa.total = nx * ny * L;
-    fa.S = 0; fa.out4 = w.out4; fa.need_gx = 0;
-    const int nb = gs::field_grid(fa, false);
-    if (nb <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
-    if ((st = hip_check(gs::launch_field(fa, false, nb, s), "field fwd (lattice)")) != GOSURF_OK) return st;
-    if ((st = hip_check(gs::launch_phi_copy(w.out4, (long long)nx * ny * L, phi + (size_t)k0 * nx * ny, s),
-                        "lattice copy")) != GOSURF_OK)
-      return st;
+                lat_bytes(nx, ny, 1));
+  // the most layers that the field kernel's point indexing takes
+  const long long points = (long long)nx * ny, most = ((1LL << 29) - 1) / points;
+  if (most < 1) return fail(GOSURF_ERR_WORKSPACE, "a z-layer of %lld points is too large", points);
+  for (long long k0 = 0; k0 < nz; k0 += most) {
+    const long long L = nz - k0 < most ? nz - k0 : most;
+    gs::PhiArgs a = phi_args(model, params, (int)(points * L), phi + (size_t)k0 * points);
+    for (int c = 0; c < 3; ++c) a.p0[c] = p0[c];
+    a.h = h; a.nx = nx; a.ny = ny; a.k0 = (int)k0;
+    if ((st = hip_check(gs::launch_phi(a, (hipStream_t)stream), "SDF of the lattice")) != GOSURF_OK) return st;
   }
   return ok();
 }

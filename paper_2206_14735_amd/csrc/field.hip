@@ -69,9 +69,9 @@ __device__ __forceinline__ void fill_load(const float* __restrict__ P, float (&v
 }
 // The four steps of the groups SLOT, SLOT + 4, ... packed for the BF16 layers,
 // group SLOT / 4 + u by wave u.
-template <int SLOT>
+template <int SLOT, int END = T_END>
 __device__ __forceinline__ void fill_bf16(const float* __restrict__ P, uint2* tab, int wave, int lane) {
-  if constexpr (SLOT < T_END) {
+  if constexpr (SLOT < END) {
     const int i = lane & 15, q = lane >> 4;
     float v[4];
 #pragma unroll
@@ -79,20 +79,20 @@ __device__ __forceinline__ void fill_bf16(const float* __restrict__ P, uint2* ta
       v[w] = wave == 0 ? table_value<SLOT>(P, w, i, q) : wave == 1 ? table_value<SLOT + 4>(P, w, i, q)
              : wave == 2 ? table_value<SLOT + 8>(P, w, i, q) : table_value<SLOT + 12>(P, w, i, q);
     tab[(SLOT / 4 + wave) * 64 + lane] = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
-    fill_bf16<SLOT + 16>(P, tab, wave, lane);
+    fill_bf16<SLOT + 16, END>(P, tab, wave, lane);
   }
 }
 
 // Fills the FP32 tables of a block (four waves): wave w takes slot SLOT + w of
 // each group, with the loads of GROUPS groups in flight at once.
-template <int SLOT, int GROUPS>
+template <int SLOT, int GROUPS, int END = T_END>
 __device__ __forceinline__ void fill_f32(const float* __restrict__ P, float* tab, int w, int lane) {
-  if constexpr (SLOT < T_END) {
+  if constexpr (SLOT < END) {
     float v[GROUPS];
     fill_load<SLOT, 0, GROUPS>(P, v, w, lane & 15, lane >> 4);
 #pragma unroll
     for (int u = 0; u < GROUPS; ++u) tab[(SLOT + 4 * u + w) * 64 + lane] = v[u];
-    fill_f32<SLOT + 4 * GROUPS, GROUPS>(P, tab, w, lane);
+    fill_f32<SLOT + 4 * GROUPS, GROUPS, END>(P, tab, w, lane);
   }
 }
 
@@ -780,6 +780,126 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !
     for (int w = 0; w < kWavesPerBlock; ++w) s += red0[w * kMlpNumel + e];
     out[e] = s;
   }
+}
+
+// ---------------------------------------------------------------- SDF alone
+// The SDF without colour or derivatives, for the lattice and the importance
+// sampler, which read nothing else.  Issue-bound like the kernels above: lattice
+// points are formed here (their rays and depths were written by one launch and the
+// SDF picked out of the forward's four outputs by another), a block's tables are a
+// third as large, and the lattice takes the one output row of the last FP32 layer as
+// a dot product (8 multiply-adds and two row swaps in place of 8 MFMAs of 32 cycles).
+// The sampler does not: its draws magnify the last bit of the SDF, so it reads the
+// one that the render computes.
+// MI355X, us: 288 x 224 x 128 points 585 in all launches -> 338 in one; 96 and 3 x
+// 12 samples of 6144 rays 93 -> 75.  Four waves per SIMD, as the compiler chooses,
+// hold the tables in registers: two or three take 10 % longer, five or more 25 %.
+template <bool BF, bool ROW>
+struct PhiSmem {
+  float tab[BF ? 1 : (ROW ? T_L3 : T_C1) * 64];
+  uint2 tabbf[BF ? (T_C1 / 4) * 64 : 1];
+  alignas(16) float bias[32 + 32 + 16];   // b1, b2, b3
+  alignas(16) float w3row0[32];
+};
+
+template <bool BF, bool LATTICE>
+__global__ __launch_bounds__(kBlock) void phi_kernel(PhiArgs A) {
+  constexpr bool ROW = LATTICE && !BF;   // the last layer as a dot product
+  __shared__ PhiSmem<BF, ROW> sm;
+  const int tid = threadIdx.x;
+  const int wave = uniform_i(tid >> 6), lane = tid & 63, q = lane >> 4, j = lane & 15;
+  if constexpr (BF) fill_bf16<0, T_C1>(A.mlp, sm.tabbf, wave, lane);
+  else if constexpr (ROW) fill_f32<0, 6, T_L3>(A.mlp, sm.tab, wave, lane);
+  else fill_f32<0, 8, T_C1>(A.mlp, sm.tab, wave, lane);
+  if (tid < 32) {
+    sm.bias[tid] = A.mlp[oB1 + tid];
+    sm.bias[32 + tid] = A.mlp[oB2 + tid];
+    sm.w3row0[tid] = A.mlp[oW3 + tid];
+  }
+  if (tid < 16) sm.bias[64 + tid] = A.mlp[oB3 + tid];
+  const LevelConst lc = level_const(A.g, q);
+  __syncthreads();
+
+  const int n_tiles = (A.total + 15) / 16;
+  for (int tile = blockIdx.x * kWavesPerBlock + wave; tile < n_tiles; tile += gridDim.x * kWavesPerBlock) {
+    const int item = tile * 16 + j;
+    const bool live = item < A.total;
+    float px = 0.f, py = 0.f, pz = 0.f;
+    if constexpr (LATTICE) {
+      // the tile's first point by uniform divisions; its lanes step over row ends
+      const int row0 = tile * 16 / A.nx;
+      int i = tile * 16 - row0 * A.nx + j, k = row0 / A.ny, y = row0 - k * A.ny;
+      while (i >= A.nx) {
+        i -= A.nx;
+        if (++y == A.ny) { y = 0; ++k; }
+      }
+      if (live) {
+        px = mad_norm((float)i, A.h, A.p0[0]);
+        py = mad_norm((float)y, A.h, A.p0[1]);
+        pz = mad_norm((float)(A.k0 + k), A.h, A.p0[2]);
+      }
+    } else if (live) {
+      const int ray = A.ray_of[item];
+      const float tt = A.t[item];
+      px = mad_norm(tt, A.r[3 * ray + 0], A.o[3 * ray + 0]);
+      py = mad_norm(tt, A.r[3 * ray + 1], A.o[3 * ray + 1]);
+      pz = mad_norm(tt, A.r[3 * ray + 2], A.o[3 * ray + 2]);
+    }
+    const bool valid = live && inside_box(A.g, px, py, pz);
+    LevelSample ls;
+    locate(A.g, lc, px, py, pz, ls);
+    float zl[4], G[4][3];
+    interp<false, BF>(A.grid, A.grid_bf16, ls, valid, zl, G);
+    v4f zb = v4f{zl[0], zl[1], zl[2], zl[3]};
+    v4f h1[2], h2[2];
+    layer<BF, 2, 1>(sm, T_L1, &zb, h1, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) h1[b] = relu_bias(h1[b], sm.bias + 16 * b, q);
+    layer<BF, 2, 2>(sm, T_L2, h1, h2, lane);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) h2[b] = relu_bias(h2[b], sm.bias + 32 + 16 * b, q);
+    float phi;
+    if constexpr (!ROW) {
+      v4f ob;
+      layer<BF, 1, 2>(sm, T_L3, h2, &ob, lane);
+      phi = plus_bias(ob, sm.bias + 64, q)[0];
+    } else {
+      const float4 w0 = *reinterpret_cast<const float4*>(sm.w3row0 + 4 * q);
+      const float4 w1 = *reinterpret_cast<const float4*>(sm.w3row0 + 16 + 4 * q);
+      const float s0 = fmaf(w0.w, h2[0][3], fmaf(w0.z, h2[0][2], fmaf(w0.y, h2[0][1], w0.x * h2[0][0])));
+      const float s1 = fmaf(w1.w, h2[1][3], fmaf(w1.z, h2[1][2], fmaf(w1.y, h2[1][1], w1.x * h2[1][0])));
+      phi = sum_rows(s0 + s1) + sm.bias[64];
+    }
+    if (q == 0 && live) A.phi[item] = phi;
+  }
+}
+
+template <bool BF, bool LATTICE>
+static hipError_t launch_phi_t(const PhiArgs& a, hipStream_t st) {
+  thread_local int cached_dev = -1, cached_blocks = 0;
+  int dev = 0, cus = 0, per_cu = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev != cached_dev) {
+    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&phi_kernel<BF, LATTICE>),
+                                                     kBlock, 0);
+    if (e != hipSuccess) return e;
+    cached_dev = dev;
+    cached_blocks = cus * (per_cu > 0 ? per_cu : 1);
+  }
+  // at most one resident round, every wave with as many tiles as the others
+  const int tiles = (a.total + 15) / 16, waves = cached_blocks * kWavesPerBlock;
+  const int per = (tiles + waves - 1) / waves;
+  const int blocks = (tiles + per * kWavesPerBlock - 1) / (per * kWavesPerBlock);
+  hipLaunchKernelGGL((phi_kernel<BF, LATTICE>), dim3(blocks), dim3(kBlock), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_phi(const PhiArgs& a, hipStream_t st) {
+  if (a.total < 1) return hipErrorInvalidValue;
+  if (a.ray_of == nullptr) return a.grid_bf16 ? launch_phi_t<true, true>(a, st) : launch_phi_t<false, true>(a, st);
+  return a.grid_bf16 ? launch_phi_t<true, false>(a, st) : launch_phi_t<false, false>(a, st);
 }
 
 // The levels summed in LDS, as rows of block partials for the sums that end the

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kImpWaves * 64) void importance_step_kernel(ImpArgs
     if (i < n) {
       const float tt = A.t[base + i];
       ts[i] = tt;
-      ph[c] = A.phi[(base + i) * A.phi_stride];
+      ph[c] = A.phi[base + i];
       val[c] = inside_box(A.g, mad_norm(tt, r[0], o[0]), mad_norm(tt, r[1], o[1]), mad_norm(tt, r[2], o[2]));
       if (!val[c]) ph[c] = 0.f;
     }
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kImpWaves * 64) void importance_merge_kernel(ImpMer
     for (int j = 0; j < nb; ++j) cnt += tb[j] < x;
     const size_t dst = bo + i + cnt;
     A.t_out[dst] = x;
-    if (A.p_out) A.p_out[dst] = A.pa[(ba + i) * A.pa_stride];
+    if (A.p_out) A.p_out[dst] = A.pa[ba + i];
     if (A.ray_of_out) A.ray_of_out[dst] = m;
   }
   // new samples: rank among the new ones (by value, then index) + current samples at or before
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kImpWaves * 64) void importance_merge_kernel(ImpMer
     }
     const size_t dst = bo + own + lo;
     A.t_out[dst] = y;
-    if (A.p_out) A.p_out[dst] = A.pb[(bb + lane) * A.pb_stride];
+    if (A.p_out) A.p_out[dst] = A.pb[bb + lane];
     if (A.ray_of_out) A.ray_of_out[dst] = m;
   }
   if (A.seg_out && lane == 0) {

@@ -1,8 +1,7 @@
 // Surface extraction: the reconstructed surface is the zero level set of phi
-// (Sec. 3.1).  The SDF is evaluated on a regular lattice by the forward field
-// kernel (each lattice row along x is a ray with direction (1, 0, 0) and
-// samples t_i = i h), and the surface is extracted by marching tetrahedra:
-// every cube of 8 lattice points is split into the six tetrahedra around its
+// (Sec. 3.1).  The SDF is evaluated on a regular lattice by the field kernel that
+// computes nothing else, and the surface is extracted by marching tetrahedra: every
+// cube of 8 lattice points is split into the six tetrahedra around its
 // main diagonal (corners c = bx + 2 by + 4 bz), so neighbouring cubes split
 // their shared faces the same way and the surface is closed.
 #include "device.h"
@@ -10,35 +9,6 @@
 #include "args.h"
 
 namespace gs {
-
-// rows (j, k0 + kk) of a slab of `layers` z-layers as rays; lattice point
-// x = p0 + h (i, j, k) rounded as the field kernel forms o + t r
-__global__ __launch_bounds__(256) void lattice_rays_kernel(LatticeArgs A) {
-  const long long n = (long long)A.nx * A.ny * A.layers;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int i = (int)(e % A.nx);
-    const long long row = e / A.nx;
-    A.t[e] = __fmul_rn((float)i, A.h);
-    A.ray_of[e] = (int)row;
-    if (i == 0) {
-      const int j = (int)(row % A.ny), k = A.k0 + (int)(row / A.ny);
-      A.o[3 * row + 0] = A.p0[0];
-      A.o[3 * row + 1] = mad_norm((float)j, A.h, A.p0[1]);
-      A.o[3 * row + 2] = mad_norm((float)k, A.h, A.p0[2]);
-      A.r[3 * row + 0] = 1.f;
-      A.r[3 * row + 1] = 0.f;
-      A.r[3 * row + 2] = 0.f;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void phi_copy_kernel(const float* __restrict__ out4, long long n,
-                                                       float* __restrict__ phi) {
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n;
-       e += (long long)gridDim.x * blockDim.x)
-    phi[e] = out4[4 * e];
-}
 
 __global__ void zero_count_kernel(unsigned* count) { *count = 0u; }
 
@@ -159,15 +129,6 @@ static int grid_for(long long n) {
   return (int)(b < 65536 ? (b > 0 ? b : 1) : 65536);
 }
 
-hipError_t launch_lattice_rays(const LatticeArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(lattice_rays_kernel, dim3(grid_for((long long)a.nx * a.ny * a.layers)), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_phi_copy(const float* out4, long long n, float* phi, hipStream_t st) {
-  hipLaunchKernelGGL(phi_copy_kernel, dim3(grid_for(n)), dim3(256), 0, st, out4, n, phi);
-  return hipGetLastError();
-}
 
 hipError_t launch_marching_tets(const MtArgs& a, hipStream_t st) {
   if (a.nx < 2 || a.ny < 2 || a.nz < 2) return hipErrorInvalidValue;

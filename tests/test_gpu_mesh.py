@@ -103,6 +103,44 @@ def test_sdf_lattice_matches_oracle_over_several_slabs():
     check_close("lattice phi", phi.cpu().numpy().reshape(-1), ref, FWD_TOL)
 
 
+@pytest.mark.parametrize("dims", [(2, 2, 2), (2, 3, 7), (3, 2, 41), (15, 4, 2), (16, 3, 3), (17, 2, 5), (33, 31, 4)])
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_lattice_rows_of_any_length(dims, precision):
+    """Tiles of 16 points run over row and layer ends.  In FP32 the points match
+    the oracle; in BF16, where the lattice's layers are those of the forward,
+    they equal its SDF at the same points bit for bit, outside the box too."""
+    from oracle import step as ostep
+    G = _G()
+    L, fr, b, grid, mlp = sphere_case(M=8, S=0, grid_std=0.3)
+    nx, ny, nz = dims
+    prec = G.BF16 if precision == "bf16" else G.FP32
+    h = 0.05 if prec == G.FP32 else 0.2
+    p0 = (L.p0[0] + 0.013, L.p0[1] + 0.021, L.p0[2] + 0.007)
+    g, m = grid.cuda().contiguous(), mlp.cuda().contiguous()
+    model = G.make_model(L, prec)
+    kw = {}
+    if prec == G.BF16:
+        kw["grid_bf16"] = torch.empty(g.shape, dtype=torch.bfloat16, device="cuda")
+        G.gosurf_refresh_bf16(g, kw["grid_bf16"])
+    phi = G.gosurf_sdf_lattice(model, g, m, p0, h, dims, **kw).cpu().numpy().reshape(-1)
+    x = _f32_lattice(p0, h, dims)
+    if prec == G.FP32:
+        assert np.all(x <= np.asarray(L.p1)) and np.all(x >= np.asarray(L.p0))
+        check_close("lattice phi", phi, MS.field_sdf(grid.numpy(), mlp.numpy(), L)(x), FWD_TOL)
+        return
+    o = x.reshape(nz * ny, nx, 3)[:, 0].astype(np.float32)
+    r = np.tile(np.float32([1, 0, 0]), (nz * ny, 1))
+    t = np.tile(np.arange(nx, dtype=np.float32) * np.float32(h), nz * ny)
+    zero = np.zeros((0, 3), np.float32)
+    rays = ostep.Batch(o, r, np.zeros_like(o), np.zeros(nz * ny, np.float32), t,
+                       np.arange(0, nx * ny * nz + 1, nx, dtype=np.int32), zero, zero)
+    db = G.RayBatch.from_host(rays)
+    out = G.gosurf_forward(model, g, m, db, G.make_loss_cfg((10.0, 1.0, 10.0, 1.0, 0.0, 0.0)),
+                           G.workspace_for(model, db.M, db.total, db.S), **kw)
+    ref = out.sample_values(db.total)[0].cpu().numpy()
+    assert np.array_equal(phi, ref)
+
+
 def test_mesh_of_the_field_matches_oracle():
     G = _G()
     L, fr, b, grid, mlp = sphere_case(M=8, S=0, grid_std=0.3)
