@@ -44,31 +44,38 @@ enum : int {
   CV_END = 64
 };
 
-__device__ float colour_table_value(const float* __restrict__ P, int slot, int l) {
-  int tb, nbi;
-  if (slot < CV2) { tb = CV1; nbi = 1; }
-  else if (slot < CV3) { tb = CV2; nbi = 2; }
-  else if (slot < CV3T) { tb = CV3; nbi = 2; }
-  else if (slot < CV2T) { tb = CV3T; nbi = 1; }
-  else if (slot < CV1T) { tb = CV2T; nbi = 2; }
-  else { tb = CV1T; nbi = 2; }
-  const int rel = slot - tb;
-  const int bo = rel / (4 * nbi), s = rel % (4 * nbi);
-  const int i = 16 * bo + (l & 15);                       // output row
-  const int k = 16 * (s >> 2) + 4 * (l >> 4) + (s & 3);   // input row
-  switch (tb) {
-    case CV1: return k < 9 ? P[oV1 + i * 9 + k] : 0.f;
-    case CV2: return P[oV2 + i * 32 + k];
-    case CV3: return i < 3 ? P[oV3 + i * 32 + k] : 0.f;
-    case CV3T: return k < 3 ? P[oV3 + k * 32 + i] : 0.f;
-    case CV2T: return P[oV2 + k * 32 + i];
-    default: return i < 9 ? P[oV1 + k * 9 + i] : 0.f;
+// Value of lane (i, q) of slot SLOT + w, w = 0..3: every fourth slot starts a
+// group of four K steps of one block pair, known at compile time: output row
+// i + 16 bo, input row 16 bi + 4 q + w.
+template <int SLOT>
+__device__ __forceinline__ float colour_table_value(const float* __restrict__ P, int w, int i, int q) {
+  constexpr int tb = SLOT < CV2 ? CV1 : SLOT < CV3 ? CV2 : SLOT < CV3T ? CV3 : SLOT < CV2T ? CV3T
+                     : SLOT < CV1T ? CV2T : CV1T;
+  constexpr int nbi = (tb == CV1 || tb == CV3T) ? 1 : 2;
+  constexpr int g = (SLOT - tb) / 4, bo = g / nbi, bi = g % nbi;
+  i += 16 * bo;
+  const int k = 16 * bi + 4 * q + w;
+  if constexpr (tb == CV1) return k < 9 ? P[oV1 + i * 9 + k] : 0.f;
+  else if constexpr (tb == CV2) return P[oV2 + i * 32 + k];
+  else if constexpr (tb == CV3) return i < 3 ? P[oV3 + i * 32 + k] : 0.f;
+  else if constexpr (tb == CV3T) return k < 3 ? P[oV3 + k * 32 + i] : 0.f;
+  else if constexpr (tb == CV2T) return P[oV2 + k * 32 + i];
+  else return i < 9 ? P[oV1 + k * 9 + i] : 0.f;
+}
+
+// Fills the tables of a block: wave w takes slot SLOT + w of each group of four.
+template <int SLOT, int END>
+__device__ __forceinline__ void fill_colour(const float* __restrict__ P, float* tab, int w, int lane) {
+  if constexpr (SLOT < END) {
+    const float v = colour_table_value<SLOT>(P, w, lane & 15, lane >> 4);
+    fill_colour<SLOT + 4, END>(P, tab, w, lane);   // the loads of all groups are in flight before the first store
+    tab[(SLOT + w) * 64 + lane] = v;
   }
 }
 
 struct ColourSmem {
   float tab[CV_END * 64];
-  float bias[32 + 32 + 16];         // e1, e2, e3 (padded to 16)
+  alignas(16) float bias[32 + 32 + 16];   // e1, e2, e3 (padded to 16)
 };
 constexpr int kColourScrFloats = 2048;   // per wave: operand transposes (backward)
 constexpr int kColourMaxBlocks = 2048;   // rows of the weight-gradient partials
@@ -119,10 +126,7 @@ __device__ __forceinline__ void colour_tile(const ColourArgs& A, const ColourSme
     }
   }
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    cf[k] += __shfl_xor(cf[k], 16, 64);
-    cf[k] += __shfl_xor(cf[k], 32, 64);
-  }
+  for (int k = 0; k < 6; ++k) cf[k] = sum_rows(cf[k]);
   const float rn = sqrtf(rx * rx + ry * ry + rz * rz);
   const float d0 = rx / rn, d1 = ry / rn, d2 = rz / rn;
   v4f in0 = v4f{0.f, 0.f, 0.f, 0.f};
@@ -134,18 +138,15 @@ __device__ __forceinline__ void colour_tile(const ColourArgs& A, const ColourSme
   v4f h1[2], h2[2], ob;
   layer_f32<2, 1>(sm.tab, CV1, &in0, h1, lane);
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) h1[b][r] = fmaxf(h1[b][r] + sm.bias[16 * b + 4 * q + r], 0.f);
+  for (int b = 0; b < 2; ++b) h1[b] = relu_bias(h1[b], sm.bias + 16 * b, q);
   layer_f32<2, 2>(sm.tab, CV2, h1, h2, lane);
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) h2[b][r] = fmaxf(h2[b][r] + sm.bias[32 + 16 * b + 4 * q + r], 0.f);
+  for (int b = 0; b < 2; ++b) h2[b] = relu_bias(h2[b], sm.bias + 32 + 16 * b, q);
   layer_f32<1, 2>(sm.tab, CV3, h2, &ob, lane);
-  v4f cb;
+  ob = plus_bias(ob, sm.bias + 64, q);
+  float cb[3];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) cb[r] = sigmoidf_(ob[r] + sm.bias[64 + 4 * q + r]);
+  for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_(ob[r]);
 
   if constexpr (!BWD) {
     if (q == 0 && live) {
@@ -212,30 +213,34 @@ __device__ __forceinline__ void colour_tile(const ColourArgs& A, const ColourSme
     merge_step<kRowShl2, 2>(val, segid, j);
     merge_step<kRowShl4, 4>(val, segid, j);
     merge_step<kRowShl8, 8>(val, segid, j);
-    // The writers stage their two corners by rank in the wave's scratch (8
-    // floats per corner, 6 used), then 8 lanes write one corner: the 6
-    // features of a vertex lie in one aligned 32-byte row, so each corner is
-    // one request of an atomic instruction instead of six.
+    // The writers stage their two corners in the wave's scratch (8 floats per
+    // corner, 6 used); the runs are the same in the four lane groups, so the 8
+    // corners of a run are 8 jobs, x-neighbours side by side.  8 lanes write one
+    // corner, one aligned 32-byte row: an atomic instruction covers a run, and
+    // the rows of x-neighbours, every other time one 64-byte line, join in one
+    // request (6144 x 96 samples: 172 us, 210 us with a run's corners apart and
+    // the tables' slots decoded at run time).
     const bool writer = head && valid;
-    const unsigned long long wm = __ballot(writer);
-    const int nw = __popcll(wm);
+    const unsigned wm = (unsigned)(__ballot(writer) >> (16 * q)) & 0xffffu;
+    const int nw = __popc(wm);
     int* dsti = reinterpret_cast<int*>(scrA + 1024);   // [128] rows, after the [128][8] values
     wave_lds_fence();   // the transposes' reads of the scratch are complete
     if (writer) {
-      const int rank = __popcll(wm & ((1ull << lane) - 1ull));
+      const int rank = __popc(wm & ((1u << j) - 1u));
 #pragma unroll
       for (int cc = 0; cc < 2; ++cc) {
+        const int k = 8 * rank + 4 * (q & 1) + 2 * cc + (q >> 1);   // (by, bz, bx)
 #pragma unroll
-        for (int k = 0; k < 6; ++k) scrA[16 * rank + 8 * cc + k] = val[6 * cc + k];
-        dsti[2 * rank + cc] = (int)crow[cc];
+        for (int f = 0; f < 6; ++f) scrA[8 * k + f] = val[6 * cc + f];
+        dsti[k] = (int)crow[cc];
       }
     }
     wave_lds_fence();
-    const int jobs = 2 * nw, f = lane & 7;
-    for (int base = 0; base < jobs; base += 8) {
-      const int k = base + (lane >> 3);
+    const int f = lane & 7;
+    for (int run = 0; run < nw; ++run) {
+      const int k = 8 * run + (lane >> 3);
       wait_vmem_at_most<1>();   // as in the field kernel's scatter: a bounded number in flight
-      if (k < jobs && f < 6) atomic_add_global(A.grad_cgrid + 8 * (long long)dsti[k] + f, scrA[8 * k + f]);
+      if (f < 6) atomic_add_global(A.grad_cgrid + 8 * (long long)dsti[k] + f, scrA[8 * k + f]);
     }
     wave_lds_fence();   // the next tile reuses the scratch
   }
@@ -248,7 +253,7 @@ __global__ __launch_bounds__(256) void colour_kernel(ColourArgs A) {
   float* scr = reinterpret_cast<float*>(smem_raw + sizeof(ColourSmem));
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, j = lane & 15;
-  fill_batched<256>(sm.tab, CV_END * 64, tid, [&](int e) { return colour_table_value(A.cmlp, e >> 6, e & 63); });
+  fill_colour<0, BWD ? CV_END : CV3T>(A.cmlp, sm.tab, wave, lane);
   if (tid < 32) {
     sm.bias[tid] = A.cmlp[oE1 + tid];
     sm.bias[32 + tid] = A.cmlp[oE2 + tid];
