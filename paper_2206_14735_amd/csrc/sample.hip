@@ -99,14 +99,16 @@ __device__ __forceinline__ void pick_ray(const SampleArgs& A, int m, float o[3],
 __device__ __forceinline__ void sample_point(const SampleArgs& A, int p);
 
 // Rays of a wave.  A wave's time is mostly the latency of its chain (pixel,
-// pose, span, draw, rank), so large batches share it between up to 8 rays.  On
-// MI355X 65536 rays of about 27 samples take 18.5 us with 8 (30 us with one
-// Philox block per sample and two rays a wave); from 1024 to 6144 rays, one to
-// four rays a wave differ by less than 2 us, and one leaves no CU idle.
+// pose, span, draw, rank), so batches that fill the chip otherwise share it
+// between up to 8 rays.  On MI355X 65536 rays of about 27 samples take 18.5 us
+// with 8 (30 us with one Philox block per sample and two rays a wave).  Whole
+// sampling calls with one ray a wave below 16384 rays and with two from 4096 on:
+// 12133 proposal rays 40.8 and 39.0 us, 16000 importance rays 120 and 114 us; from
+// 1024 to 6144 rays they differ by less than 1 us.
 constexpr int kRaysPerWave = 8;
 
 inline int rays_per_wave(int M) {
-  const int n = M / 8192;
+  const int n = M / 2048;
   return n < 1 ? 1 : (n > kRaysPerWave ? kRaysPerWave : n);
 }
 

@@ -185,10 +185,11 @@ def test_proposal_driven_sampling(n_free, depth_check, extend, edge, plain_n):
     assert np.array_equal(batch.ray_of.cpu().numpy()[:seg[-1]], np.repeat(np.arange(M), lens))
 
 
-@pytest.mark.parametrize("M,plain_n,n_free", [(16384, (3, 2), None), (24577, (61, 0), None), (65539, (7, 6), None),
+@pytest.mark.parametrize("M,plain_n,n_free", [(4096, (64, 32), None), (16384, (3, 2), None), (24577, (61, 0), None),
+                                              (65539, (7, 6), None), (6145, (1, 0), 0), (10241, (16, 8), 5),
                                               (16385, (16, 8), 5), (40000, (1, 0), 0), (65539, (40, 16), 5)])
 def test_rays_that_share_a_wave_are_sampled_as_alone(M, plain_n, n_free):
-    """Batches of 16384 rays and more give each wave 2 to 8 neighbouring rays;
+    """Batches of 4096 rays and more give each wave 2 to 8 neighbouring rays;
     a ray's samples depend on its number alone, so the batch starts with the
     smaller batch's rays bit for bit, and (plain) ends with the oracle's."""
     G = _G()
