@@ -39,7 +39,7 @@ def parse():
     ap.add_argument("--colour-grid", action="store_true",
                     help="the paper's colour path: colour grid at the finest level + view direction, 9-32-32-3")
     ap.add_argument("--grad-copies", action="store_true",
-                    help="the backward scatters the large levels into x/y-parity gradient copies")
+                    help="the model flag grad_copies: accepted, changes the workspace size only")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-rays", type=int, default=0,
                     help="rays of the oracle baseline's sample (0: the workload's whole batch)")

@@ -495,12 +495,10 @@ gosurf_status gosurf_proposal_backward(const gosurf_model* model, const float* g
    meshes it on a 1 cm lattice.
 
    The SDF on the lattice p0 + h (i, j, k), i < nx, j < ny, k < nz, stored in
-   phi [nz][ny][nx] (x fastest), evaluated by the forward field kernel at the
-   model's precision (lattice point x = p0 + i h rounded as float32 i*h + p0).
-   Points outside the grid box get the decoder's value at zero features.  The
-   lattice is processed in z-slabs as large as the workspace allows
-   (gosurf_lattice_workspace_bytes(nx, ny, layers) bytes hold `layers`
-   z-layers; at least one layer is needed).
+   phi [nz][ny][nx] (x fastest), evaluated at the model's precision (lattice
+   point x = p0 + i h rounded as float32 i*h + p0).  Points outside the grid box
+   get the decoder's value at zero features.  The workspace must have at least
+   gosurf_lattice_workspace_bytes(nx, ny, 1) bytes; nothing is kept in it.
    Errors: NULL, SHAPE, VALUE, WORKSPACE, HIP. */
 size_t gosurf_lattice_workspace_bytes(int32_t nx, int32_t ny, int32_t layers);
 gosurf_status gosurf_sdf_lattice(const gosurf_model* model, const gosurf_params* params, const float p0[3],
