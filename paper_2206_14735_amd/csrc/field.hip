@@ -323,6 +323,14 @@ constexpr int kPrivMaxFloats = 4096;   // LDS budget for privatised levels (1024
 constexpr int kFieldMaxBlocksFwd = 4096;   // rows of the smoothness partials in the workspace
 constexpr int kFieldMaxBlocksBwd = 2048;   // rows of the decoder / level partials in the workspace
 
+// Whether both points of the lane's smoothness pair are valid (the partner is
+// lane j ^ 8).  The read stands outside the conjunction: behind it, lanes whose
+// own point is outside would be masked off, and their partners read no answer.
+__device__ __forceinline__ bool valid_pair(bool valid) {
+  const int other = __shfl_xor((int)valid, 8, 64);
+  return valid && other;
+}
+
 // One wave-tile: MODE 0 = 16 ray samples, MODE 1 = 8 smoothness pairs (lanes
 // j < 8 hold x, lanes j >= 8 hold x + eps of the same pair).  POSE (backward
 // only): also dL/dx of every ray sample, for camera pose refinement.
@@ -466,7 +474,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
       float d0 = gx[0] - __shfl_xor(gx[0], 8, 64);
       float d1 = gx[1] - __shfl_xor(gx[1], 8, 64);
       float d2 = gx[2] - __shfl_xor(gx[2], 8, 64);
-      const bool pv = valid && __shfl_xor((int)valid, 8, 64);
+      const bool pv = valid_pair(valid);
       const float sq = d0 * d0 + d1 * d1 + d2 * d2;
       if (q == 0 && j < 8 && pv) smooth_acc += sq;
       if (A.pair_terms && q == 0 && j < 8 && live) A.pair_terms[item] = pv ? sq : 0.f;
@@ -620,7 +628,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
   } else {
     // smoothness pair: d|g(x) - g(x+eps)|^2 / dg at either point is
     // 2 (own gradient - partner's gradient); smooth_coef carries the 2.
-    const bool pv = valid && __shfl_xor((int)valid, 8, 64);
+    const bool pv = valid_pair(valid);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const float d = gx[a] - __shfl_xor(gx[a], 8, 64);

@@ -526,3 +526,23 @@ def test_losses_are_the_sums_of_their_terms(M):
     assert got[7] == nd
     np.testing.assert_allclose(got[:6], exact, rtol=34 * 2.0 ** -24, atol=1e-30)
     np.testing.assert_allclose(got[6], np.dot(LAMBDAS, exact), rtol=40 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("M", [64, 1250])
+def test_pairs_that_leave_the_box_contribute_nothing(M):
+    """Smoothness pairs with the first, the second or both points outside the box
+    have no loss and no gradient, whether the gradient is scattered directly (64
+    rays) or through records (1250 rays, over 1024 points for each of 64 bins)."""
+    L, _, b, grid, mlp = sphere_case(M=M, S=600, grid_std=0.3)
+    rng = np.random.default_rng(7)
+    xs = rng.uniform(-1.2, 1.2, (600, 3))
+    axis, side = rng.integers(0, 3, 600), rng.choice([-1.0, 1.0], 600)
+    face = side * (L.p1[0] + rng.uniform(-0.003, 0.003, 600))
+    xs[np.arange(600), axis] = np.where(rng.random(600) < 0.6, face, xs[np.arange(600), axis])
+    b = ostep.Batch(b.o, b.r, b.rgb, b.depth, b.t, b.seg, xs.astype(np.float32), b.eps)
+    x2 = (b.xs + b.eps).astype(np.float32)
+    inside = lambda x: np.all((x >= np.float32(L.p0)) & (x <= np.float32(L.p1)), 1)  # noqa: E731
+    for first, second in ((True, False), (False, True), (False, False)):
+        assert np.sum((inside(b.xs) == first) & (inside(x2) == second)) > 10
+    b = _clear(grid, mlp, L, b)
+    compare(run_device(L, b, grid, mlp), *oracle_pair(grid, mlp, L, b), case=(L, b, mlp))
