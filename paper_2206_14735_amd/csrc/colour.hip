@@ -206,7 +206,8 @@ __device__ __forceinline__ void colour_tile(const ColourArgs& A, const ColourSme
 #pragma unroll
       for (int k = 0; k < 6; ++k) val[6 * cc + k] = valid ? wc[cc] * g[k] : 0.f;
     const int key = valid ? (int)row0 : -1 - j;   // an invalid lane is a run of its own
-    const bool head = (j == 0) || key != dpp_i<kRowShr1>(key);
+    const int kprev = dpp_i<kRowShr1>(key);   // (read with all lanes active: behind the test, lane 1 would read 0)
+    const bool head = (j == 0) || key != kprev;
     const unsigned grp = (unsigned)(__ballot(head) >> (16 * q)) & 0xffffu;
     const int segid = __popc(grp & ((2u << j) - 1u));
     merge_step<kRowShl1, 1>(val, segid, j);

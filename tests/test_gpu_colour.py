@@ -105,3 +105,31 @@ def test_colour_grid_path_rejects_bf16_and_missing_parameters():
     st = G.lib().gosurf_forward(C.byref(model), C.byref(p), C.byref(db.c()), C.byref(lc), C.byref(out.c()),
                                 G._ptr(ws), ws.numel(), None)
     assert st == 1 and b"colour_grid" in G.lib().gosurf_last_error()
+
+
+def test_second_sample_of_a_tile_in_the_first_cell():
+    """Rays of one tile (16 samples) whose second sample enters the grid's first
+    cell, cell (0, 0, 0) of row 0, from another cell or from outside the box:
+    what the samples there contribute goes to that cell's corners, not to
+    those of the tile's first sample."""
+    L, fr, b0, grid, mlp = sphere_case(M=64, S=0, grid_std=0.3)
+    cg, cm = synth.init_colour(L, seed=2, grid_std=0.5)
+    rng = np.random.default_rng(4)
+    M, v, lo = 64, L.voxels[-1], L.p0[0]
+    o, r = rng.uniform(lo + 0.1 * v, lo + 0.9 * v, (M, 3)), rng.uniform(-0.02, 0.02, (M, 3))
+    out = np.arange(M) % 2 == 1
+    o[:, 0] = np.where(out, lo - v, lo + 2 * v)
+    r[:, 0] = np.where(out, 1.0, -1.0)
+    t = np.concatenate([rng.uniform(0.2, 0.9, (M, 1)), np.sort(rng.uniform(1.05, 1.95, (M, 15)), 1)], 1) * v
+    b = ostep.Batch(o.astype(np.float32), r.astype(np.float32), b0.rgb, np.full(M, 1.5 * v, np.float32),
+                    t.astype(np.float32).ravel(), np.arange(0, 16 * M + 1, 16).astype(np.int32),
+                    np.zeros((0, 3), np.float32), np.zeros((0, 3), np.float32))
+    b, nr, _ = clear_of_kinks(grid.numpy(), mlp.numpy(), L, b, max_frac=0.25, colour_grid=cg.numpy(), colour_mlp=cm.numpy())
+    kw = dict(colour_grid=cg.numpy(), colour_mlp=cm.numpy())
+    ref = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, **kw)
+    r32 = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, dtype=torch.float32, **kw)
+    dev = _device(L, b, grid, mlp, cg, cm)
+    check_parity("c_hat", dev["c_hat"], _np(ref["c_hat"]), _np(r32["c_hat"]), FWD_TOL)
+    check_parity("grad colour grid", dev["grad_cg"], _np(ref["grad_colour_grid"]), _np(r32["grad_colour_grid"]),
+                 GRAD_TOL)
+    assert np.all(dev["grad_cg"][_np(ref["grad_colour_grid"]) == 0] == 0)
