@@ -11,6 +11,7 @@ namespace gs {
 
 constexpr int kMaxBins = 1 << 20;        // entries of the counting tables
 constexpr int kWinVerts = 912;           // vertices of a window (all levels): 14.25 KB of float4
+constexpr int kWinEdge = 9;              // vertices of a window along z: a flush holds a column in registers
 constexpr int kQueues = 64;              // work counters of the scatter, 64 bytes apart
 constexpr unsigned kDense = 16;          // records for which a bin gets the window
 constexpr int kSmallVerts = 1024;        // vertices of the small levels together, at most

@@ -18,8 +18,9 @@ namespace gs {
 // edge covers `ratio` cells of level l.  Where the edges of cells and bins
 // coincide (ratio or its inverse whole, as in grids whose voxels divide each
 // other) it uses ratio + 1 vertices (at least 2), otherwise one cell more.
-// The largest shift up to 3 whose windows fit is taken; at shift 2 they always
-// do (5^3 vertices of the finest level, at most 6^3 of each coarser one).
+// The largest shift up to 3 whose windows fit the LDS and, along z, the columns
+// of a flush is taken; at shift 2 they always do (5^3 vertices of the finest
+// level, at most 6^3 of each coarser one).
 void plan_bins(const Grid& g, Bins& B) {
   B.level = 0;
   for (int l = 1; l < 4; ++l)
@@ -27,7 +28,7 @@ void plan_bins(const Grid& g, Bins& B) {
   const int f = B.level;
   const int n[3] = {g.nx[f], g.ny[f], g.nz[f]};
   for (B.shift = 3;; --B.shift) {
-    int verts = 0;
+    int verts = 0, edge = 0;
     for (int l = 0; l < 4; ++l) {
       const float r = (float)(1 << B.shift) * (g.voxel[f] / g.voxel[l]);
       const float up = floorf(r + 0.5f), inv = floorf(1.f / r + 0.5f);
@@ -44,8 +45,9 @@ void plan_bins(const Grid& g, Bins& B) {
         c *= B.wd[l][a];
       }
       verts += c;
+      if (B.wd[l][2] > edge) edge = B.wd[l][2];
     }
-    if (verts <= kWinVerts || B.shift == 0) break;
+    if ((verts <= kWinVerts && edge <= kWinEdge) || B.shift == 0) break;
   }
   for (int a = 0; a < 3; ++a) {
     B.nb[a] = ((n[a] - 2) >> B.shift) + 1;
@@ -176,7 +178,6 @@ struct WindowLevel {
 // walked in columns along z: the lanes cover (x, y, feature) of a slab with
 // features innermost, so that a 64-byte chunk of the gradient is one request,
 // and read their column before they write any of it.
-constexpr int kWinEdge = 9;   // most vertices of a window per axis (2^3 cells)
 __device__ __forceinline__ void flush_window(const WindowLevel& L, float* win, int verts, int bin, int nbx,
                                              int nby, int lane) {
   const int bx = bin % nbx, by = (bin / nbx) % nby, bz = bin / (nbx * nby);
