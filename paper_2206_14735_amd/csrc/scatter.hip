@@ -153,12 +153,16 @@ __device__ __forceinline__ int window_origin(int c, float ratio, int n, int wd) 
 // base[offset bytes] += v in the lanes whose v is not 0 (base is the same in
 // every lane).  Written out, as the compiler puts a branch around a memory
 // operation under a lane mask: with one in each of a window's 68 columns a flush
-// took 13000 cycles.
+// took 13000 cycles.  A memory instruction must not read a scalar register within
+// five wait states of a vector instruction that wrote it (base may come from a
+// readlane or a register spilled to a lane), and the compiler does not look into
+// the block: it keeps that distance from its own start.
 __device__ __forceinline__ void add_nonzero(float* base, unsigned offset, float v) {
   unsigned long long saved;
   asm volatile(
       "v_cmp_neq_f32_e32 vcc, 0, %1\n\t"
       "s_and_saveexec_b64 %0, vcc\n\t"
+      "s_nop 2\n\t"
       "global_atomic_add_f32 %2, %1, %3\n\t"
       "s_mov_b64 exec, %0"
       : "=&s"(saved)
