@@ -19,7 +19,7 @@ LevelSums small_sums(const Grid& g, const ScatterRecords& r);
 void plan_privatised_levels(FieldArgs& a, int counts[4]);
 int priv_max_floats();
 void plan_bins(const Grid& g, Bins& b);
-bool records_pay(const Bins& b, long long points, int far);
+long long records_from(const Bins& b, int far);
 long long plan_tables(const Grid& g, ScatterRecords& r, float* tables);
 long long max_tables();
 hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st);
@@ -551,7 +551,8 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.g = g;
   int counts[4];
   gs::plan_privatised_levels(fa, counts);
-  const bool records = gs::records_pay(rec.bins, (long long)b->total + 2LL * S, 4 - __builtin_popcount(fa.priv_mask));
+  const bool records =
+      (long long)b->total + 2LL * S >= gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask));
   if (records) fa.priv_mask = fa.priv_floats = 0;
   if (records) {
     const long long n_tables = gs::plan_tables(g, rec, w.tables);

@@ -57,21 +57,32 @@ void plan_bins(const Grid& g, Bins& B) {
   B.inv_v = 1.f / g.voxel[f];
 }
 
-// Whether to scatter through records.  Without them the field kernel adds to
-// memory itself, about 8 requests per sample overlapped with its decoders; with
-// them it writes records of up to 160 bytes and the scatter's time comes on top.
-// `points`: samples and pair points; `far`: levels the field kernel would not
-// accumulate in LDS.  Measured (backward call, direct / records):
-//   room, 3 cm, 96 samples per ray: 6144 rays 371 / 430 us, 16384 rays 854 / 878,
-//   32768 rays 1659 / 1572, 65536 rays 3210 / 2931; 65536 rays of 24-96 samples
-//   in BF16 1001 / 942; 2 cm and 2^20 pairs, 65536 x 128: 6360 / 4620;
-//   two levels kept in LDS (6 cm mapping grid), 65536 x 96: 2561 / 2676.
-// On a small grid the direct adds queue at few addresses (sphere, 64 bins): 512
-// rays of 64 samples 94 / 92 us, 2048 rays 151 / 126, 16384 rays 726 / 456.
-bool records_pay(const Bins& B, long long points, int far) {
+// The points (samples and pair points) from which a batch is scattered through
+// records.  Without them the field kernel adds to memory itself, about 8 requests
+// per sample overlapped with its decoders; with them it writes records of up to
+// 160 bytes, and the scatter's time comes on top, with a share for every bin that
+// is touched.  `far`: levels the field kernel would not accumulate in LDS.
+// Measured (MI355X, backward call, us, direct / records), 96 samples per ray and
+// 16384 pairs unless stated:
+//   room at 3 cm, 16128 bins: 0.59 M samples 352 / 388, 1.57 M 820 / 803,
+//     2.1 M 1077 / 1023, 3.1 M 1579 / 1460, 6.3 M 3050 / 2701; no pairs: 1.25 M
+//     631 / 662, 1.57 M 786 / 789, 1.82 M 912 / 891
+//   at 2 cm, 54432 bins: no pairs 0.79 M 423 / 600, 1.57 M 807 / 908; 2^18 pairs
+//     2.1 M 1512 / 1287, 4.2 M 2517 / 2169
+//   at 1 cm, 435456 bins, no pairs: 3.1 M 1638 / 2800, 6.3 M 3231 / 4456
+//   two levels kept in LDS (6 cm mapping grid): 3.1 M 1122 / 1278, 6.3 M 2241 / 2425
+// On a small grid the direct adds queue at few addresses:
+//   64 bins, no pairs: 33 k 53 / 68, 66 k 72 / 80, 77 k 82 / 85, 96 k 98 / 90,
+//     131 k 123 / 100; 4096 pairs: 74 k 91 / 85, 91 k 103 / 91
+//   125 bins: 64 k 74 / 87, 128 k 118 / 103, 192 k 166 / 122
+// The lines lie where the two meet in FP32.  BF16 decoders leave more of the
+// direct adds uncovered, and records win earlier there (0.59 M at 3 cm: 356 / 306,
+// 1.57 M at 2 cm: 822 / 716): one line serves both, on the safe side.
+long long records_from(const Bins& B, int far) {
   const long long bins = (long long)B.nb[0] * B.nb[1] * B.nb[2];
-  if (bins <= 256) return points >= 512 * bins;
-  return far >= 3 && points >= (1LL << 21) && points >= 100 * bins;
+  if (bins <= 256) return 50000 + 256 * bins;
+  if (far < 3) return 1LL << 62;
+  return 48 * bins > (1LL << 21) ? 48 * bins : 1LL << 21;
 }
 
 // Slots of the counting table (about 2^14 for grids of fewer bins, see

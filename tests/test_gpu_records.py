@@ -7,6 +7,7 @@ import pytest
 import synth
 from tests.helpers import f32_layout, sphere_case
 from tests.test_gpu_parity import _clear, compare, oracle_pair, run_device
+from tests.test_record_plan_cpu import records_from
 
 pytestmark = pytest.mark.gpu
 
@@ -28,17 +29,32 @@ def _thin_case(voxels, size, M, S=777):
     return L, _clear(grid, mlp, L, b), grid, mlp
 
 
-@pytest.mark.parametrize("M", [200, 1250])
+@pytest.mark.parametrize("M", [900, 1250])
 @pytest.mark.parametrize("voxels,size", [((0.64, 0.32, 0.083, 0.08), (0.24, 2.56, 2.56)),
                                          ((0.7, 0.3, 0.077, 0.07), (0.2, 2.1, 2.1))])
 def test_close_levels_in_a_thin_box(voxels, size, M):
     """A bin of 8^3 cells touches up to ten vertices per axis of a level whose
     voxel is a little larger than the finest, and a thin box leaves room for such
     a window; such grids take bins of 4^3 cells.  Both batches are dense enough
-    for records at 8^3 cells, the larger one at 4^3 as well."""
+    for records with the 16 bins of 8^3 cells, the larger one with the 64 of 4^3."""
     L, b, grid, mlp = _thin_case(voxels, size, M)
     assert 7 < 8 * voxels[3] / voxels[2] < 8
-    for shift in (3, 2)[:1 if M == 200 else 2]:
-        bins = int(np.prod([((n - 2) >> shift) + 1 for n in L.dims[3]]))
-        assert bins <= 256 and len(b.t) + 2 * len(b.xs) >= (512 if M == 200 else 1024) * bins
+    points = len(b.t) + 2 * len(b.xs)
+    assert points >= 50000 + 256 * 16 and (points >= records_from(L)) == (M == 1250)
     compare(run_device(L, b, grid, mlp), *oracle_pair(grid, mlp, L, b), case=(L, b, mlp))
+
+
+@pytest.mark.parametrize("grid", ["nested", "unaligned"])
+def test_records_match_oracle(grid):
+    """Batches dense enough for records: levels whose cells nest in the bins, and
+    levels whose cells straddle bin faces; smoothness pairs with points in
+    different bins; bins below and above the 16 records from which a bin gets a
+    window."""
+    L, _, b, grid_, mlp = sphere_case(M=1250, S=777, grid_std=0.3)
+    if grid == "unaligned":
+        # 2.1 m box; a bin edge (8 x 0.07 m) is 0.7, 1.4 and 1.93 cells of the coarser levels
+        L = f32_layout(synth.GridLayout((-1.05,) * 3, (1.05,) * 3, [0.8, 0.4, 0.29, 0.07], [(n, n, n) for n in (4, 7, 9, 31)]))
+        grid_, mlp = synth.init_params(L, seed=5, grid_std=0.3)
+    b = _clear(grid_, mlp, L, b)
+    assert len(b.t) + 2 * len(b.xs) >= records_from(L)
+    compare(run_device(L, b, grid_, mlp), *oracle_pair(grid_, mlp, L, b), case=(L, b, mlp))

@@ -7,6 +7,7 @@ import re
 import numpy as np
 import pytest
 
+import synth
 from paper_2206_14735_amd import gosurf as G
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(G.__file__)), "csrc")
@@ -28,16 +29,37 @@ def _constant(name):
     return int(re.search(rf"constexpr (?:int|unsigned) {name} = (\d+);", src).group(1))
 
 
-def _plan(voxels, size):
+def _bins(p0, p1, voxels, dims):
     g, b = Grid(), Bins()
     for a in range(3):
-        g.p0[a], g.p1[a] = 0.0, size[a]
+        g.p0[a], g.p1[a] = p0[a], p1[a]
     for l, v in enumerate(voxels):
         g.voxel[l] = v
         for a, f in enumerate((g.nx, g.ny, g.nz)):
-            f[l] = max(2, math.ceil(round(size[a] / v, 6)) + 1)
+            f[l] = dims[l][a]
     G.lib()._ZN2gs9plan_binsERKNS_4GridERNS_4BinsE(C.byref(g), C.byref(b))
     return b
+
+
+def _plan(voxels, size):
+    dims = [[max(2, math.ceil(round(s / v, 6)) + 1) for s in size] for v in voxels]
+    return _bins([0.0] * 3, size, voxels, dims)
+
+
+def records_from(layout):
+    """Points (samples, and two per smoothness pair) from which a batch on this
+    layout is scattered through records."""
+    b = _bins(layout.p0, layout.p1, layout.voxels, layout.dims)
+    kept = far = 0
+    for d in layout.dims:   # levels the other way keeps on chip: coarsest first, 1024 vertices together
+        n = d[0] * d[1] * d[2]
+        if kept + n <= 1024:
+            kept += n
+        else:
+            far += 1
+    f = G.lib()._ZN2gs12records_fromERKNS_4BinsEi
+    f.restype = C.c_longlong
+    return f(C.byref(b), far)
 
 
 @pytest.mark.parametrize("thin", [0, 1, 2, None])
@@ -58,3 +80,23 @@ def test_windows_fit_the_lds_and_the_flush(thin):
         assert sum(b.wd[l][0] * b.wd[l][1] * b.wd[l][2] for l in range(4)) <= verts
         assert max(b.wd[l][2] for l in range(4)) <= edge, (vox, size, b.shift)
         assert b.shift >= 2
+
+
+# Backward times on MI355X in FP32, us: (voxels coarsest first, box, samples, pairs, direct, through records)
+ROOM, CUBE = ((0.0, 0.0, 0.0), (8.0, 6.0, 3.0)), ((-1.0,) * 3, (1.0,) * 3)
+MEASURED = [
+    ((0.03, 0.06, 0.24, 0.96), ROOM, 589824, 16384, 352, 388), ((0.03, 0.06, 0.24, 0.96), ROOM, 1248000, 0, 631, 662),
+    ((0.03, 0.06, 0.24, 0.96), ROOM, 3145728, 16384, 1579, 1460), ((0.03, 0.06, 0.24, 0.96), ROOM, 6291456, 16384, 3050, 2701),
+    ((0.02, 0.06, 0.24, 0.96), ROOM, 786432, 0, 423, 600), ((0.02, 0.06, 0.24, 0.96), ROOM, 1572864, 0, 807, 908),
+    ((0.02, 0.06, 0.24, 0.96), ROOM, 3072000, 1 << 18, 1979, 1693), ((0.02, 0.06, 0.24, 0.96), ROOM, 4194304, 1 << 18, 2517, 2169),
+    ((0.01, 0.06, 0.24, 0.96), ROOM, 3145728, 0, 1638, 2800), ((0.01, 0.06, 0.24, 0.96), ROOM, 6291456, 0, 3231, 4456),
+    ((0.08, 0.16, 0.32, 0.64), CUBE, 32768, 0, 53, 68), ((0.08, 0.16, 0.32, 0.64), CUBE, 65536, 0, 72, 80),
+    ((0.08, 0.16, 0.32, 0.64), CUBE, 65536, 4096, 91, 85), ((0.08, 0.16, 0.32, 0.64), CUBE, 131072, 0, 123, 100),
+    ((0.05, 0.1, 0.2, 0.4), CUBE, 64000, 0, 74, 87), ((0.05, 0.1, 0.2, 0.4), CUBE, 128000, 0, 118, 103),
+]
+
+
+@pytest.mark.parametrize("voxels,box,samples,pairs,direct,records", MEASURED)
+def test_records_are_taken_where_they_were_faster(voxels, box, samples, pairs, direct, records):
+    layout = synth.padded_layout(*box, voxels)
+    assert (samples + 2 * pairs >= records_from(layout)) == (records < direct)
