@@ -411,8 +411,9 @@ gosurf_status gosurf_forward_static(const gosurf_model* model, const gosurf_para
    `total` are clamped to it.
    The grid gradient is scattered either by float32 atomics as samples are
    processed or, for batches dense enough, through records grouped by spatial
-   bins and summed on chip; the sizes decide, and the result is the same
-   gradient up to the order of float32 additions.
+   bins and summed on chip; the sizes decide (of a batch with `prop`, whose
+   `total` is a capacity, the count seg[M] on the device), and the result is
+   the same gradient up to the order of float32 additions.
    model->grad_copies = 1 changes no result; it needs each level past the first
    1024 vertices to have at most 2048 x 2048 x 512 vertices and all copies to
    fit 2^31 floats (else VALUE).

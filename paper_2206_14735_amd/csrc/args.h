@@ -16,9 +16,23 @@ struct EdgeCheck {
   float edge;
 };
 
+// Whether a backward pass scatters through records.  The host decides by the
+// number of samples where it knows it.  Of a batch drawn with a proposal it knows
+// the capacity, up to three times the samples there are; where the capacity
+// would do, the kernels of both ways are launched, and each decides by the
+// count on the device (all read the same) whether it runs or ends at once.
+struct RecordChoice {
+  const int* seg_end;   // sample count on the device, or nullptr: the host's word holds
+  int records;
+  int total;            // capacity
+  int from;             // records from this many samples on
+  __device__ __forceinline__ bool operator()() const { return records && (!seg_end || min(*seg_end, total) >= from); }
+};
+
 // Scatter records of the backward, grouped by bin.  An item is a ray sample
 // (0 .. total - 1) or a point of smoothness pair p (total + 2 p, total + 2 p + 1).
 struct ScatterRecords {
+  RecordChoice choice;
   Bins bins;
   int2* place;            // [total + 2 S]: table slot and rank inside it; slot < 0: no record
   unsigned* queue;        // [kQueues][16]: work counters of the scatter
@@ -80,9 +94,9 @@ struct FieldArgs {
   int colour;             // ray mode: 1 = colour from the geometry decoder's features; 0 = no colour
                           // here (the paper's colour path runs in its own kernel)
   const int* seg_end;     // ray mode: device copy of the sample count (seg[M]); total is then a capacity
-  // backward: with scatter records (rec.place non-null) the kernel writes them,
-  // at the place the binning gave each item, and the scatter kernel adds them to
-  // the gradient; without, it adds to grad_grid itself.  Then the levels in
+  // backward: one kernel writes scatter records, at the place the binning gave
+  // each item, and the scatter kernel adds them to the gradient; the other adds
+  // to grad_grid itself (rec.choice says which of them runs).  Then the levels in
   // priv_mask are accumulated in LDS per block, each at its float offset of the
   // block's LDS area
   ScatterRecords rec;
@@ -190,16 +204,19 @@ struct LevelSums {
 
 // The sums that end a backward pass.
 struct GradReduceArgs {
-  const float* mlp_part;   // [rows][kMlpNumel] block partials
-  int rows;
+  RecordChoice choice;
+  const float* mlp_part;   // [rows][kMlpNumel] block partials, of rec_rows rows with records
+  int rows, rec_rows;
   float* mlp_tmp;          // [kSumRows][kMlpNumel]
   const float* ray_dv;     // [M]
   int M;
   float* ray_part;         // [64][8]
   float* grad_mlp;
-  LevelSums lev;           // floats = 0: none
-  const float* lev_part;   // [rows][floats] block partials, or nullptr if lev_tmp is there already
-  float* lev_tmp;          // [kSumRows][floats]
+  LevelSums lev;           // without records (floats = 0: none)
+  const float* lev_part;   // [rows][lev.floats] block partials
+  float* lev_tmp;          // [kSumRows][lev.floats]
+  LevelSums rec_lev;       // with records (floats = 0: none)
+  const float* rec_tmp;    // [kSumRows][rec_lev.floats], written by the scatter
   float* grad_grid;
 };
 

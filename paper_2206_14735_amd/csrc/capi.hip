@@ -13,7 +13,7 @@
 
 namespace gs {
 
-hipError_t launch_field(const FieldArgs& a, bool bwd, int blocks, hipStream_t st);
+hipError_t launch_field(const FieldArgs& a, bool bwd, bool rec, int blocks, hipStream_t st);
 LevelSums privatised_sums(const FieldArgs& a, const int counts[4]);
 LevelSums small_sums(const Grid& g, const ScatterRecords& r);
 void plan_privatised_levels(FieldArgs& a, int counts[4]);
@@ -24,7 +24,7 @@ long long plan_tables(const Grid& g, ScatterRecords& r, float* tables);
 long long max_tables();
 hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st);
 hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st);
-int field_grid(const FieldArgs& a, bool bwd);
+int field_grid(const FieldArgs& a, bool bwd, bool rec);
 hipError_t launch_render(const RenderArgs& a, bool bwd, hipStream_t st);
 hipError_t launch_loss_reduce(const float* ray_partial, int M, const float* smooth_partial, int n_sp, int S,
                               const float lam[6], float* losses, float* ray_part, hipStream_t st);
@@ -412,10 +412,10 @@ gosurf_status forward_launch(const gosurf_model* model, const gosurf_params* par
   fa.grad_phi = out->grad_phi; fa.pair_terms = out->pair_terms;
   fa.colour = model->colour_mode == GOSURF_COLOUR_DECODED;
   if (loss->lambda[5] == 0.f) fa.S = 0;   // the smoothness pairs are skipped
-  const int nb = gs::field_grid(fa, false);
+  const int nb = gs::field_grid(fa, false, false);
   if (nb <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
   mark(GOSURF_KERNEL_FIELD_FWD, true, s);
-  if ((st = hip_check(gs::launch_field(fa, false, nb, s), "field fwd")) != GOSURF_OK) return st;
+  if ((st = hip_check(gs::launch_field(fa, false, false, nb, s), "field fwd")) != GOSURF_OK) return st;
   mark(GOSURF_KERNEL_FIELD_FWD, false, s);
   if (model->colour_mode == GOSURF_COLOUR_GRID) {
     gs::ColourArgs ca{};
@@ -551,10 +551,15 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.g = g;
   int counts[4];
   gs::plan_privatised_levels(fa, counts);
-  const bool records =
-      (long long)b->total + 2LL * S >= gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask));
-  if (records) fa.priv_mask = fa.priv_floats = 0;
+  const long long from = gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask)) - 2LL * S;
+  const bool records = b->total >= from;
+  // a batch with prop may hold fewer samples than `total`: its count decides, and
+  // both ways are launched
+  const bool counted = records && b->prop != nullptr;
+  const bool direct = !records || counted;
   if (records) {
+    rec.choice.records = 1; rec.choice.total = b->total; rec.choice.from = from > 0 ? (int)from : 0;
+    rec.choice.seg_end = counted ? b->seg + b->M : nullptr;
     const long long n_tables = gs::plan_tables(g, rec, w.tables);
     rec.place = w.place; rec.first = w.bin_first; rec.cap = (long long)b->total + 2LL * S;
     rec.pos = w.rec_pos; rec.gv = w.rec_gv; rec.dz = w.rec_dz; rec.a = w.rec_a;
@@ -580,10 +585,13 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.rec = rec; fa.grad_grid = grads->grid; fa.mlp_partial = w.mlp_partial;
   fa.priv_partial = w.priv_partial;
   fa.smooth_coef = b->S > 0 ? 2.f * loss->lambda[5] * loss_scale / (float)b->S : 0.f;
-  const int nb = gs::field_grid(fa, true);
-  if (nb <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
+  gs::FieldArgs fr = fa;   // the way through records
+  fr.priv_mask = fr.priv_floats = 0;
+  const int nb = direct ? gs::field_grid(fa, true, false) : 1, nr = records ? gs::field_grid(fr, true, true) : 1;
+  if (nb <= 0 || nr <= 0) return fail(GOSURF_ERR_HIP, "field grid: the occupancy query failed");
   mark(GOSURF_KERNEL_FIELD_BWD, true, s);
-  if ((st = hip_check(gs::launch_field(fa, true, nb, s), "field bwd")) != GOSURF_OK) return st;
+  if (direct && (st = hip_check(gs::launch_field(fa, true, false, nb, s), "field bwd")) != GOSURF_OK) return st;
+  if (records && (st = hip_check(gs::launch_field(fr, true, true, nr, s), "field bwd")) != GOSURF_OK) return st;
   if (records) {
     gs::ScatterArgs sa{};
     sa.g = g; sa.rec = rec; sa.grad_grid = grads->grid;
@@ -595,11 +603,12 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
                       "ray gradients")) != GOSURF_OK)
     return st;
   gs::GradReduceArgs gr{};
-  gr.mlp_part = w.mlp_partial; gr.rows = nb; gr.mlp_tmp = w.colsum_tmp; gr.ray_dv = w.ray_dv; gr.M = b->M;
+  gr.choice = rec.choice; gr.mlp_part = w.mlp_partial; gr.rows = nb; gr.rec_rows = nr; gr.mlp_tmp = w.colsum_tmp; gr.ray_dv = w.ray_dv; gr.M = b->M;
   gr.ray_part = w.ray_part; gr.grad_mlp = grads->mlp; gr.grad_grid = grads->grid;
-  gr.lev = records ? gs::small_sums(g, rec) : gs::privatised_sums(fa, counts);
-  gr.lev_part = records ? nullptr : w.priv_partial;
-  gr.lev_tmp = records ? rec.small : w.colsum_tmp + 64 * (size_t)gs::kMlpNumel;
+  if (direct) gr.lev = gs::privatised_sums(fa, counts);
+  gr.lev_part = w.priv_partial; gr.lev_tmp = w.colsum_tmp + 64 * (size_t)gs::kMlpNumel;
+  if (records) gr.rec_lev = gs::small_sums(g, rec);
+  gr.rec_tmp = rec.small;
   if ((st = hip_check(gs::launch_grad_reduce(gr, s), "grad reduce")) != GOSURF_OK) return st;
   if (cgrid) {
     // the colour path: its own kernel on the colour seeds; its decoder partials

@@ -674,6 +674,8 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
 // wave's only add to their queue (65536 x 96: 3.21 ms with two, 3.35 with three).
 template <bool BWD, bool BF, bool POSE, bool REC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !POSE ? 3 : 2))) void field_kernel(FieldArgs A) {
+  if constexpr (BWD)
+    if (A.rec.choice() != REC) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   FieldSmem<BF, BWD, REC>& sm = *reinterpret_cast<FieldSmem<BF, BWD, REC>*>(smem_raw);
   const int tid = threadIdx.x;
@@ -984,13 +986,13 @@ static int resident_blocks(const FieldArgs& a) {
 // Grid of a field launch over `total` ray samples (16 per tile) and `S` pairs
 // (8 per tile): one block per 4 tiles, at most one resident round (the tile
 // loop covers the rest; a partial second round leaves the machine half
-// empty), and at most the workspace's partial rows.  0 on a HIP error.
-int field_grid(const FieldArgs& a, bool bwd) {
+// empty), and at most the workspace's partial rows.  rec: the backward that writes
+// records.  0 on a HIP error.
+int field_grid(const FieldArgs& a, bool bwd, bool rec) {
   const bool bf = a.grid_bf16 != nullptr;
   const int tiles = (a.total + 15) / 16 + (a.S + 7) / 8;
   int blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
   const bool pose = bwd && a.grad_x != nullptr;
-  const bool rec = bwd && a.rec.place != nullptr;
   int resident;
   if (!bwd) resident = bf ? resident_blocks<false, true, false, false>(a)
                           : resident_blocks<false, false, false, false>(a);
@@ -1020,17 +1022,17 @@ static hipError_t launch_field_t(const FieldArgs& a, int blocks, hipStream_t st)
 }
 
 template <bool BF>
-static hipError_t launch_field_bwd(const FieldArgs& a, int blocks, hipStream_t st) {
-  const bool pose = a.grad_x != nullptr, rec = a.rec.place != nullptr;
+static hipError_t launch_field_bwd(const FieldArgs& a, bool rec, int blocks, hipStream_t st) {
+  const bool pose = a.grad_x != nullptr;
   if (pose) return rec ? launch_field_t<true, BF, true, true>(a, blocks, st)
                        : launch_field_t<true, BF, true, false>(a, blocks, st);
   return rec ? launch_field_t<true, BF, false, true>(a, blocks, st)
              : launch_field_t<true, BF, false, false>(a, blocks, st);
 }
 
-hipError_t launch_field(const FieldArgs& a, bool bwd, int blocks, hipStream_t st) {
+hipError_t launch_field(const FieldArgs& a, bool bwd, bool rec, int blocks, hipStream_t st) {
   const bool bf = a.grid_bf16 != nullptr;
-  if (bwd) return bf ? launch_field_bwd<true>(a, blocks, st) : launch_field_bwd<false>(a, blocks, st);
+  if (bwd) return bf ? launch_field_bwd<true>(a, rec, blocks, st) : launch_field_bwd<false>(a, rec, blocks, st);
   return bf ? launch_field_t<false, true, false, false>(a, blocks, st)
             : launch_field_t<false, false, false, false>(a, blocks, st);
 }

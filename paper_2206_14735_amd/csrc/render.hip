@@ -363,6 +363,7 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
     dalpha[c] = R.alpha[c] > 0.f ? R.T[c] * (g[c] - Rk) : 0.f;
   }
   const float s = R.s;
+  const bool records = A.rec.choice();
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     if (c >= nch) {
@@ -413,7 +414,7 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
     const float tt = R.tt[c];
     const float px = mad_norm(tt, R.r[0], R.o[0]), py = mad_norm(tt, R.r[1], R.o[1]), pz = mad_norm(tt, R.r[2], R.o[2]);
     int2 place = make_int2(-1, 0);
-    if (A.rec.place) place = place_records(A.rec, R.valid[c] ? bin_slot(bin_of(A.rec.bins, px, py, pz), A.rec.spread, m) : -1, lane);
+    if (records) place = place_records(A.rec, R.valid[c] ? bin_slot(bin_of(A.rec.bins, px, py, pz), A.rec.spread, m) : -1, lane);
     if (k < R.n) {
       const size_t sidx = R.s0 + k;
       const float wk = R.w[c];
@@ -421,7 +422,7 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
       if (R.valid[c]) out = make_float4(dphi * sc, gc[0] * wk * sc, gc[1] * wk * sc, gc[2] * wk * sc);
       *reinterpret_cast<float4*>(A.seed4 + 4 * sidx) = out;
       *reinterpret_cast<float4*>(A.posw + 4 * sidx) = make_float4(px, py, pz, R.valid[c] ? ew * sc : 0.f);
-      if (A.rec.place) A.rec.place[sidx] = place;
+      if (records) A.rec.place[sidx] = place;
     }
   }
   // samples past the per-ray cap are not rendered: zero seeds and a position
@@ -433,7 +434,7 @@ __device__ __forceinline__ void render_bwd_ray(const RenderArgs& A, int m, int l
       *reinterpret_cast<float4*>(A.seed4 + 4 * sidx) = make_float4(0.f, 0.f, 0.f, 0.f);
       *reinterpret_cast<float4*>(A.posw + 4 * sidx) =
           make_float4(A.g.p0[0] - 1.f, A.g.p0[1] - 1.f, A.g.p0[2] - 1.f, 0.f);
-      if (A.rec.place) A.rec.place[sidx] = make_int2(-1, 0);
+      if (records) A.rec.place[sidx] = make_int2(-1, 0);
     }
   dv_acc = seg_sum<W>(dv_acc, lane);
   // d s / d v = 10 s
@@ -486,7 +487,7 @@ __device__ __forceinline__ void place_pair(const RenderArgs& A, int p) {
 __global__ __launch_bounds__(256) void render_bwd_kernel(RenderArgs A) {
   const int ray_blocks = (A.M + 3) / 4;
   if ((int)blockIdx.x >= ray_blocks) {
-    place_pair(A, ((int)blockIdx.x - ray_blocks) * 256 + (int)threadIdx.x);
+    if (A.rec.choice()) place_pair(A, ((int)blockIdx.x - ray_blocks) * 256 + (int)threadIdx.x);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -647,8 +648,9 @@ __global__ __launch_bounds__(256) void grad_stage1_kernel(GradReduceArgs A, int 
     return;
   }
   const int y = b / col_blocks, bx = b - y * col_blocks;
-  if (bx < mlp_blocks) colsum_stage1(A.mlp_part, A.rows, kMlpNumel, bx * 256 + threadIdx.x, y, A.mlp_tmp);
-  else colsum_stage1(A.lev_part, A.rows, A.lev.floats, (bx - mlp_blocks) * 256 + threadIdx.x, y, A.lev_tmp);
+  const bool records = A.choice();
+  if (bx < mlp_blocks) colsum_stage1(A.mlp_part, records ? A.rec_rows : A.rows, kMlpNumel, bx * 256 + threadIdx.x, y, A.mlp_tmp);
+  else if (!records) colsum_stage1(A.lev_part, A.rows, A.lev.floats, (bx - mlp_blocks) * 256 + threadIdx.x, y, A.lev_tmp);
 }
 
 // grads.mlp += column sums; entry v gets the per-ray dL/dv sums instead (the
@@ -656,12 +658,14 @@ __global__ __launch_bounds__(256) void grad_stage1_kernel(GradReduceArgs A, int 
 __global__ __launch_bounds__(256) void grad_stage2_kernel(GradReduceArgs A, int mlp_blocks) {
   if ((int)blockIdx.x >= mlp_blocks) {
     const int e = ((int)blockIdx.x - mlp_blocks) * 256 + threadIdx.x;
-    if (e >= A.lev.floats) return;
-    const float s = colsum_stage2(A.lev_tmp, A.lev.floats, e);
+    const bool records = A.choice();
+    const LevelSums& m = records ? A.rec_lev : A.lev;
+    if (e >= m.floats) return;
+    const float s = colsum_stage2(records ? A.rec_tmp : A.lev_tmp, m.floats, e);
 #pragma unroll
     for (int l = 0; l < 4; ++l) {
-      const int at = e - A.lev.off[l];
-      if (((A.lev.mask >> l) & 1) && at >= 0 && at < A.lev.cnt[l]) A.grad_grid[4 * A.lev.first[l] + at] += s;
+      const int at = e - m.off[l];
+      if (((m.mask >> l) & 1) && at >= 0 && at < m.cnt[l]) A.grad_grid[4 * m.first[l] + at] += s;
     }
     return;
   }
@@ -675,8 +679,9 @@ __global__ __launch_bounds__(256) void grad_stage2_kernel(GradReduceArgs A, int 
 }
 
 hipError_t launch_grad_reduce(const GradReduceArgs& a, hipStream_t st) {
-  const int mb = (kMlpNumel + 255) / 256, lb = (a.lev.floats + 255) / 256, nb = ray_sum_blocks(a.M);
-  const int cb = mb + (a.lev_part ? lb : 0);
+  const int mb = (kMlpNumel + 255) / 256, nb = ray_sum_blocks(a.M);
+  const int cb = mb + (a.lev.floats + 255) / 256;
+  const int lb = ((a.lev.floats > a.rec_lev.floats ? a.lev.floats : a.rec_lev.floats) + 255) / 256;
   hipLaunchKernelGGL(grad_stage1_kernel, dim3(kR1 * cb + nb), dim3(256), 0, st, a, mb, cb);
   hipLaunchKernelGGL(grad_stage2_kernel, dim3(mb + lb), dim3(256), 0, st, a, mb);
   return hipGetLastError();

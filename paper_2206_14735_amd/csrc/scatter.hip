@@ -115,6 +115,9 @@ long long max_tables() { return 16 * kQueues + kMaxBins + 32 + 4LL * kSmallCopie
 // Block b sums its 1024 slots and takes its records' ranges from two running
 // totals: slots of at least kDense records from the front of the records,
 // sparse ones from their end.  The order of the blocks' ranges does not matter.
+// A batch whose count decides against records has counted none: this kernel and
+// the scatter then find no work, without a look at the choice (whose arguments
+// would add a round trip of about 1 us at their start).
 __global__ __launch_bounds__(256) void bin_first_kernel(ScatterRecords R) {
   __shared__ unsigned wsum[2][4], base[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -263,6 +266,14 @@ __device__ __forceinline__ void add4(float4* w, const float4& v) {
   *w = x;
 }
 
+// Tiles of a chunk: a wave takes one chunk of its share of the tiles, or several
+// of 32 tiles, which even out the bins' differences; small batches use fewer
+// waves, so that a window collects 4 tiles before it goes to memory.
+__host__ __device__ inline unsigned scatter_chunk(unsigned tiles, unsigned waves) {
+  const unsigned c = (tiles + waves - 1) / (4 * waves);
+  return c < 4u ? 4u : (c > 32u ? 32u : c);
+}
+
 // One wave per block: the windows are private to a wave, so nothing waits at
 // a barrier.  A wave takes chunks of consecutive tiles (16 records).
 //
@@ -274,7 +285,7 @@ __device__ __forceinline__ void add4(float4* w, const float4& v) {
 // LDS accesses keep them apart.  (LDS float atomics are served about one lane
 // per clock: 85 us of a room batch and 2 ms of 8.4 M samples, against none for
 // reads and writes.)
-__global__ __launch_bounds__(64) void scatter_kernel(ScatterArgs A, int chunk) {
+__global__ __launch_bounds__(64) void scatter_kernel(ScatterArgs A, int waves) {
   __shared__ float4 win[kWinVerts];
   __shared__ float4 st_f[64], st_dz[64], st_a[64], st_g[16];   // [record][level]
   __shared__ int st_row[64];
@@ -285,7 +296,8 @@ __global__ __launch_bounds__(64) void scatter_kernel(ScatterArgs A, int chunk) {
   const unsigned cap = (unsigned)R.cap;
   const unsigned n_front = min(R.count[R.slots], cap), n_back0 = cap - min(R.count[R.slots + 1], cap);
   const unsigned front_tiles = (n_front + 15) / 16, tiles = front_tiles + (cap - n_back0 + 15) / 16;
-  if (blockIdx.x * (unsigned)chunk >= tiles) return;
+  const unsigned chunk = scatter_chunk(tiles, waves);
+  if (blockIdx.x * chunk >= tiles) return;
 
   // staging lane: its level's sizes
   const LevelConst lc = level_const(A.g, q);
@@ -496,22 +508,19 @@ hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st) {
 }
 
 // At most one resident round of waves: 9 windows with their staging fit the
-// 160 KB of a CU.  A wave takes one chunk of its share of the tiles, or several
-// of 32 tiles, which even out the bins' differences; small batches use fewer
-// waves, so that a window collects 4 tiles before it goes to memory.
+// 160 KB of a CU.  The kernel takes its chunks from the records there are, which
+// may be fewer than the arrays hold.
 hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const long long tiles = (a.rec.cap + 15) / 16, waves = (9LL * cus + kQueues - 1) / kQueues * kQueues;
-  const long long per = (tiles + waves - 1) / waves;
-  long long chunk = per / 4;
-  chunk = chunk < 4 ? 4 : (chunk > 32 ? 32 : chunk);
+  const long long chunk = scatter_chunk((unsigned)tiles, (unsigned)waves);
   long long blocks = (tiles + chunk - 1) / chunk;
   if (blocks > waves) blocks = waves;   // a multiple of kQueues, as drawing needs
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)chunk);
+  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)waves);
   return hipGetLastError();
 }
 

@@ -3,10 +3,12 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch
 
 import synth
-from tests.helpers import f32_layout, sphere_case
-from tests.test_gpu_parity import _clear, compare, oracle_pair, run_device
+from oracle import step as ostep
+from tests.helpers import GRAD_TOL, check_parity, f32_layout, sphere_case
+from tests.test_gpu_parity import LAMBDAS, _clear, _np, compare, oracle_pair, run_device
 from tests.test_record_plan_cpu import records_from
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +60,54 @@ def test_records_match_oracle(grid):
     b = _clear(grid_, mlp, L, b)
     assert len(b.t) + 2 * len(b.xs) >= records_from(L)
     compare(run_device(L, b, grid_, mlp), *oracle_pair(grid_, mlp, L, b), case=(L, b, mlp))
+
+
+def _padded(b, capacity):
+    """A device batch of host batch b whose arrays hold `capacity` samples, as a
+    batch drawn with a proposal does: the count is in seg[M] alone."""
+    from paper_2206_14735_amd import gosurf as G
+    db = G.RayBatch.from_host(b)
+    t, ray_of = torch.full((capacity,), 0.5, device="cuda"), torch.zeros(capacity, device="cuda", dtype=torch.int32)
+    t[:db.total], ray_of[:db.total] = db.t, db.ray_of
+    db.t, db.ray_of, db.prop = t, ray_of, torch.zeros(db.M, 3, device="cuda")
+    return db
+
+
+def _gradients(model, db, grid, mlp, grad_o=None, grad_r=None, ws=None, bf=None, scale=1.0):
+    from paper_2206_14735_amd import gosurf as G
+    lc = G.make_loss_cfg(LAMBDAS)
+    if ws is None:
+        ws = G.workspace_for(model, db.M, db.total, db.S)
+    g, m = grid.cuda().contiguous(), mlp.cuda().contiguous()
+    out = G.gosurf_forward(model, g, m, db, lc, ws, grid_bf16=bf)
+    gg, gm = torch.zeros_like(g), torch.zeros_like(m)
+    G.gosurf_backward(model, g, m, db, lc, out, scale, gg, gm, ws, grid_bf16=bf, grad_o=grad_o, grad_r=grad_r)
+    torch.cuda.synchronize()
+    return (gg / scale).cpu().numpy(), (gm / scale).cpu().numpy()
+
+
+@pytest.mark.parametrize("short", [0, 1, 64 * 200])
+def test_the_samples_there_are_decide(short):
+    """A batch whose arrays hold more samples than it has: its own count decides
+    whether it is scattered through records, and either way the gradients are
+    the oracle's.  Without records nothing is written to their arrays, which end
+    the workspace."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=1100, S=777, grid_std=0.3)
+    b = _clear(grid, mlp, L, b)
+    n = records_from(L) - 2 * len(b.xs) - short
+    keep = n // 64 + 1
+    seg = np.minimum(np.asarray(b.seg)[:keep + 1], n).astype(np.int32)
+    b = ostep.Batch(b.o[:keep], b.r[:keep], b.rgb[:keep], b.depth[:keep], b.t[:n], seg, b.xs, b.eps)
+    db = _padded(b, 3 * n)
+    model = G.make_model(L)
+    ws = G.workspace_for(model, db.M, db.total, db.S)
+    ws.fill_(0x5A)
+    gg, gm = _gradients(model, db, grid, mlp, ws=ws)
+    ref, r32 = oracle_pair(grid, mlp, L, b)
+    check_parity("grad_mlp", gm, _np(ref["grad_mlp"]), _np(r32["grad_mlp"]), GRAD_TOL)
+    check_parity("grad_grid", gg, _np(ref["grad_grid"]), _np(r32["grad_grid"]), GRAD_TOL)
+    records = 128 * (db.total + 2 * db.S)   # dL/dz and d(phi)/dz of each record
+    assert ws.numel() > records
+    written = bool((ws[-records:] != 0x5A).any())
+    assert written == (short == 0)
