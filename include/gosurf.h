@@ -307,12 +307,15 @@ gosurf_status gosurf_sample_rays(const gosurf_model* model, const gosurf_frames*
                                  const gosurf_sample_cfg* cfg, gosurf_ray_batch* out,
                                  void* stream);
 
-/* Workspace bytes needed by forward/backward for a batch of these sizes: about
-   200 bytes per sample (32 of them its seeds, 168 its scatter record) and 336
-   per smoothness pair, plus 67 MB of partial sums and tables.  With
-   model->grad_copies = 1 this includes room for four gradient copies, about 64
-   bytes per vertex of every level past the first 1024 vertices (counted
-   coarsest first).
+/* Workspace bytes for forward/backward on a batch of these sizes: 32 bytes per
+   sample plus 58 MB of partial sums, and, where the model's grid and the sizes
+   let the backward scatter through records, their room: 168 bytes per sample, 336
+   per smoothness pair and 9.4 MB of tables.  Only the first part is required
+   (it is what a NULL model gives): a workspace without the records' room
+   is accepted, and the backward adds to the gradient directly.  With
+   model->grad_copies = 1 the required part includes room for four gradient
+   copies, about 64 bytes per vertex of every level past the first 1024 vertices
+   (counted coarsest first).
    Returns 0 for negative sizes or a model the copies cannot serve. */
 size_t gosurf_workspace_bytes(const gosurf_model* model, int32_t M, int32_t total, int32_t S);
 
@@ -412,8 +415,9 @@ gosurf_status gosurf_forward_static(const gosurf_model* model, const gosurf_para
    The grid gradient is scattered either by float32 atomics as samples are
    processed or, for batches dense enough, through records grouped by spatial
    bins and summed on chip; the sizes decide (of a batch with `prop`, whose
-   `total` is a capacity, the count seg[M] on the device), and the result is
-   the same gradient up to the order of float32 additions.
+   `total` is a capacity, the count seg[M] on the device), and the workspace must
+   have the records' room (see gosurf_workspace_bytes).  The result is the same
+   gradient up to the order of float32 additions.
    model->grad_copies = 1 changes no result; it needs each level past the first
    1024 vertices to have at most 2048 x 2048 x 512 vertices and all copies to
    fit 2^31 floats (else VALUE).

@@ -156,7 +156,9 @@ struct Workspace {
   float* priv_partial;    // [2048][priv_max_floats]
   float* colsum_tmp;      // [64][kMlpNumel], then [64][priv_max_floats]
   float* ray_part;        // [64][8] block partials of sums over rays
-  // scatter records (see ScatterRecords), cap = total + 2 S
+  size_t bytes;           // of all these, which every call needs
+  // scatter records (see ScatterRecords), cap = total + 2 S: only where the batch
+  // takes them and the workspace has room
   int2* place;            // [cap]
   float* tables;          // counting tables and copies of small levels (plan_tables)
   unsigned* bin_first;    // [kMaxBins]
@@ -164,7 +166,7 @@ struct Workspace {
   float4* rec_gv;         // [cap]
   float4* rec_dz;         // [cap][4]
   float4* rec_a;          // [cap][4]
-  size_t bytes;
+  size_t with_records;    // bytes of everything
 };
 
 Workspace layout(char* base, int M, int total, int S) {
@@ -182,6 +184,7 @@ Workspace layout(char* base, int M, int total, int S) {
   w.priv_partial = reinterpret_cast<float*>(take(sizeof(float) * 2048 * (size_t)gs::priv_max_floats()));
   w.colsum_tmp = reinterpret_cast<float*>(
       take(sizeof(float) * 64 * (size_t)(gs::kMlpNumel + gs::priv_max_floats())));
+  w.bytes = off;
   w.place = reinterpret_cast<int2*>(take(sizeof(int2) * cap));
   w.tables = reinterpret_cast<float*>(take(sizeof(float) * (size_t)gs::max_tables()));
   w.bin_first = reinterpret_cast<unsigned*>(take(sizeof(unsigned) * gs::kMaxBins));
@@ -189,7 +192,7 @@ Workspace layout(char* base, int M, int total, int S) {
   w.rec_gv = reinterpret_cast<float4*>(take(sizeof(float4) * cap));
   w.rec_dz = reinterpret_cast<float4*>(take(sizeof(float4) * 4 * cap));
   w.rec_a = reinterpret_cast<float4*>(take(sizeof(float4) * 4 * cap));
-  w.bytes = off;
+  w.with_records = off;
   return w;
 }
 
@@ -280,13 +283,20 @@ int64_t gosurf_batch_samples(const gosurf_sample_cfg* cfg) {
 
 size_t gosurf_workspace_bytes(const gosurf_model* model, int32_t M, int32_t total, int32_t S) {
   if (M < 0 || total < 0 || S < 0) return 0;
-  long long cf = 0;
-  if (model) {
-    if (check_model(model) != GOSURF_OK) return 0;
-    cf = model_copy_bytes(model);
-    if (cf < 0) return 0;
-  }
-  return layout(nullptr, M, total, S).bytes + (size_t)cf;
+  const Workspace w = layout(nullptr, M, total, S);
+  if (!model) return w.bytes;
+  if (check_model(model) != GOSURF_OK) return 0;
+  const long long cf = model_copy_bytes(model);
+  if (cf < 0) return 0;
+  const size_t need = w.bytes + (size_t)cf;
+  gs::FieldArgs fa{};
+  fa.g = to_grid(model);
+  int counts[4];
+  gs::plan_privatised_levels(fa, counts);
+  gs::Bins bins;
+  gs::plan_bins(fa.g, bins);
+  const bool records = total + 2LL * S >= gs::records_from(bins, 4 - __builtin_popcount(fa.priv_mask));
+  return records && w.with_records > need ? w.with_records : need;
 }
 
 gosurf_status gosurf_sample_rays(const gosurf_model* model, const gosurf_frames* fr, const gosurf_sample_cfg* c,
@@ -552,7 +562,7 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   int counts[4];
   gs::plan_privatised_levels(fa, counts);
   const long long from = gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask)) - 2LL * S;
-  const bool records = b->total >= from;
+  const bool records = b->total >= from && ws_bytes >= w.with_records;
   // a batch with prop may hold fewer samples than `total`: its count decides, and
   // both ways are launched
   const bool counted = records && b->prop != nullptr;

@@ -111,3 +111,26 @@ def test_the_samples_there_are_decide(short):
     assert ws.numel() > records
     written = bool((ws[-records:] != 0x5A).any())
     assert written == (short == 0)
+
+
+@pytest.mark.parametrize("M,asked", [(200, "without the pairs"), (1250, "without the records")])
+def test_a_workspace_without_the_records_room_serves(M, asked):
+    """What forward and backward need does not depend on the smoothness pairs,
+    nor on whether the batch would take records: without their room the gradient
+    is added to directly.  Nothing past the workspace is written."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=M, S=777, grid_std=0.3)
+    b = _clear(grid, mlp, L, b)
+    db = G.RayBatch.from_host(b)
+    assert (db.total + 2 * db.S >= records_from(L)) == (asked == "without the records")
+    model = G.make_model(L)
+    need = G.lib().gosurf_workspace_bytes(None, db.M, db.total, 0)
+    assert (G.gosurf_workspace_bytes(model, db.M, db.total, db.S) > need) == (asked == "without the records")
+    room = torch.full((need + (1 << 20),), 0x5A, device="cuda", dtype=torch.uint8)
+    gg, gm = _gradients(model, db, grid, mlp, ws=room[:need])
+    ref, r32 = oracle_pair(grid, mlp, L, b)
+    check_parity("grad_mlp", gm, _np(ref["grad_mlp"]), _np(r32["grad_mlp"]), GRAD_TOL)
+    check_parity("grad_grid", gg, _np(ref["grad_grid"]), _np(r32["grad_grid"]), GRAD_TOL)
+    assert bool((room[need:] == 0x5A).all())
+    with pytest.raises(G.GosurfError, match="workspace"):
+        _gradients(model, db, grid, mlp, ws=room[:need - 1])
