@@ -105,9 +105,16 @@ def field_unit_flops(kernel, eikonal):
     return fwd, 2 * pair_point
 
 
-def field_unit_bytes(kernel, precision):
-    """(bytes per ray sample, bytes per smoothness pair) of one field kernel."""
+def field_unit_bytes(kernel, precision, records=False):
+    """(bytes per ray sample, bytes per smoothness pair) of one field kernel, or
+    of the record scatter.  A backward through records writes a sample's record
+    (position, dL/dz, d(phi)/dz, dL/d(grad phi): 160 bytes, 96 for a pair point)
+    at its 8-byte place; without, it adds to the 32 corners of 16 bytes."""
     g = 32 * CORNER_BYTES[precision]            # 4 levels x 8 corners
+    if kernel == "scatter":
+        return 160.0, 192.0
+    if kernel == "field_bwd" and records:
+        return g + 168.0 + 32.0, 2 * g + 208.0 + 24.0
     if kernel == "field_bwd":
         return g + 512.0 + 32.0, 2 * g + 1024.0 + 24.0
     return g + 28.0, 2 * g + 24.0
@@ -635,9 +642,13 @@ def main():
     print(f"# per call (ms): {per}", file=sys.stderr, flush=True)
 
     # per-kernel durations: HIP events recorded by the library around each launch
+    # (the scatter's where the workspace has its records' room)
+    plain = G.make_model(w.layout(), rec.model.precision)
+    records = (G.gosurf_workspace_bytes(plain, w.M, rec.total, w.S) >
+               G.lib().gosurf_workspace_bytes(None, w.M, rec.total, w.S))
     kern = {}
     for name, kid in (("field_fwd", G.KERNEL_FIELD_FWD), ("field_bwd", G.KERNEL_FIELD_BWD),
-                      ("adam", G.KERNEL_ADAM)):
+                      ("adam", G.KERNEL_ADAM)) + ((("scatter", G.KERNEL_SCATTER),) if records else ()):
         pairs = []
         for _ in range(a.steps):
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -666,7 +677,7 @@ def main():
     pairs = w.S
 
     def field_bytes(k):
-        per_sample, per_pair = field_unit_bytes(k, w.precision)
+        per_sample, per_pair = field_unit_bytes(k, w.precision, records)
         return per_sample * samples_now + per_pair * pairs
 
     roofs = {
@@ -678,6 +689,9 @@ def main():
         "adam": roofline("adam", BYTES_PER_PARAM_ADAM * (rec.grid.numel() + rec.mlp.numel()), kern["adam"],
                          "adam_kernel (gosurf_adam_step)"),
     }
+    if records:
+        roofs["scatter"] = roofline("scatter", field_bytes("scatter"), kern["scatter"],
+                                    "scatter_kernel (gosurf_backward: scatter records)")
     eikonal = w.lambdas[4] > 0
 
     def mfma_roofline(k, label):
@@ -694,7 +708,7 @@ def main():
         "field_bwd_mfma": mfma_roofline("field_bwd", "field_kernel<backward>: decoder FLOPs on MFMA"),
         "field_fwd_mfma": mfma_roofline("field_fwd", "field_kernel<forward>: decoder FLOPs on MFMA"),
     }
-    dominant = max(("field_fwd", "field_bwd", "adam"), key=lambda k: kern[k])
+    dominant = max(roofs, key=lambda k: kern[k])
     roof = roofs[dominant]
 
     if a.calibrate_copy:

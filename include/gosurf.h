@@ -270,8 +270,10 @@ typedef struct {
 typedef enum {
   GOSURF_KERNEL_NONE = 0,
   GOSURF_KERNEL_FIELD_FWD = 1,     /* forward field kernel of gosurf_forward (samples and smoothness pairs) */
-  GOSURF_KERNEL_FIELD_BWD = 2,     /* backward field kernel of gosurf_backward (samples and smoothness pairs) */
-  GOSURF_KERNEL_ADAM = 4           /* the dense Adam kernel of gosurf_adam_step */
+  GOSURF_KERNEL_FIELD_BWD = 2,     /* backward field kernel of gosurf_backward (samples and smoothness pairs; where
+                                      the count on the device picks one of two variants, the launches of both) */
+  GOSURF_KERNEL_ADAM = 4,          /* the dense Adam kernel of gosurf_adam_step */
+  GOSURF_KERNEL_SCATTER = 8        /* the record scatter of gosurf_backward, where the batch takes records */
 } gosurf_kernel_id;
 
 /* Measurement hook (this thread only): the next launch of `kernel` is

@@ -266,7 +266,7 @@ const char* gosurf_last_error(void) { return g_err; }
 
 gosurf_status gosurf_time_kernel(int32_t kernel, void* start_event, void* stop_event) {
   if (kernel != GOSURF_KERNEL_NONE && kernel != GOSURF_KERNEL_FIELD_FWD && kernel != GOSURF_KERNEL_FIELD_BWD &&
-      kernel != GOSURF_KERNEL_ADAM)
+      kernel != GOSURF_KERNEL_ADAM && kernel != GOSURF_KERNEL_SCATTER)
     return fail(GOSURF_ERR_VALUE, "unknown kernel %d", kernel);
   g_timed_kernel = (start_event && stop_event) ? kernel : GOSURF_KERNEL_NONE;
   g_ev_start = static_cast<hipEvent_t>(start_event);
@@ -602,12 +602,14 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   mark(GOSURF_KERNEL_FIELD_BWD, true, s);
   if (direct && (st = hip_check(gs::launch_field(fa, true, false, nb, s), "field bwd")) != GOSURF_OK) return st;
   if (records && (st = hip_check(gs::launch_field(fr, true, true, nr, s), "field bwd")) != GOSURF_OK) return st;
+  mark(GOSURF_KERNEL_FIELD_BWD, false, s);
   if (records) {
     gs::ScatterArgs sa{};
     sa.g = g; sa.rec = rec; sa.grad_grid = grads->grid;
+    mark(GOSURF_KERNEL_SCATTER, true, s);
     if ((st = hip_check(gs::launch_scatter(sa, s), "grid scatter")) != GOSURF_OK) return st;
+    mark(GOSURF_KERNEL_SCATTER, false, s);
   }
-  mark(GOSURF_KERNEL_FIELD_BWD, false, s);
   if (ray_grads &&
       (st = hip_check(gs::launch_ray_xgrad(w.seed4, b->t, b->seg, b->M, b->total, grads->ray_o, grads->ray_r, s),
                       "ray gradients")) != GOSURF_OK)

@@ -134,3 +134,36 @@ def test_a_workspace_without_the_records_room_serves(M, asked):
     assert bool((room[need:] == 0x5A).all())
     with pytest.raises(G.GosurfError, match="workspace"):
         _gradients(model, db, grid, mlp, ws=room[:need - 1])
+
+
+def test_kernel_times_do_not_overlap():
+    """The times of the backward field kernel and of the record scatter are those
+    of their own launches: together they stay below the whole call's."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=8192, S=777, grid_std=0.3)
+    db = G.RayBatch.from_host(b)
+    model, lc = G.make_model(L), G.make_loss_cfg(LAMBDAS)
+    assert db.total >= records_from(L)
+    ws = G.workspace_for(model, db.M, db.total, db.S)
+    g, m = grid.cuda(), mlp.cuda()
+    gg, gm = torch.zeros_like(g), torch.zeros_like(m)
+    out = G.gosurf_forward(model, g, m, db, lc, ws)
+    event = lambda: torch.cuda.Event(enable_timing=True)  # noqa: E731
+    times = {}
+    for name, kernel in (("field", G.KERNEL_FIELD_BWD), ("scatter", G.KERNEL_SCATTER), ("call", None)):
+        best = np.inf
+        for _ in range(10):
+            e0, e1 = event(), event()
+            e0.record()
+            e1.record()
+            if kernel is not None:
+                G.gosurf_time_kernel(kernel, e0, e1)
+            G.gosurf_backward(model, g, m, db, lc, out, 1.0, gg, gm, ws)
+            if kernel is None:
+                e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times[name] = best
+    print(times, flush=True)
+    assert times["field"] > 0 and times["scatter"] > 0
+    assert times["field"] + times["scatter"] <= times["call"]
