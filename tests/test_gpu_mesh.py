@@ -222,3 +222,27 @@ def test_bf16_lattice_and_importance_follow_fp32():
     print(f"BF16 importance depths: median difference {float(d.median()):.2e} m", flush=True)
     assert float(d.median()) < 1e-2
     assert t16.shape[1] == n0 + 36
+
+
+def test_lattice_of_several_launches():
+    """A layer of 2^28 points fills a launch, so that the second layer has one of
+    its own: points drawn from both match the oracle (a layer's step moves phi by
+    more than the tolerance)."""
+    G = _G()
+    L, fr, b, grid, mlp = sphere_case(M=8, S=0, grid_std=0.3)
+    dims, h = (1 << 14, 1 << 14, 2), 2.5 / (1 << 14)
+    p0 = (L.p0[0] + 0.013, L.p0[1] + 0.021, L.p0[2] + 0.077)
+    ws = torch.empty(G.gosurf_lattice_workspace_bytes(dims[0], dims[1], 1), dtype=torch.uint8, device="cuda")
+    phi = G.gosurf_sdf_lattice(G.make_model(L), grid.cuda().contiguous(), mlp.cuda().contiguous(), p0, h, dims,
+                               workspace=ws)
+    rng = np.random.default_rng(3)
+    i, j, k = rng.integers(0, dims[0], 4096), rng.integers(0, dims[1], 4096), rng.integers(0, 2, 4096)
+    i[:4], j[:4], k[:4] = (0, dims[0] - 1, 0, dims[0] - 1), (0, dims[1] - 1, 0, dims[1] - 1), (0, 0, 1, 1)
+    got = phi[torch.from_numpy(k).cuda(), torch.from_numpy(j).cuda(), torch.from_numpy(i).cuda()].cpu().numpy()
+    f = np.float32
+    x = np.stack([f(n) * f(h) + f(p) for n, p in zip((i, j, k), p0)], 1)
+    assert np.all(x <= np.asarray(L.p1)) and np.all(x >= np.asarray(L.p0))
+    ref = MS.field_sdf(grid.numpy(), mlp.numpy(), L)(x)
+    moved = MS.field_sdf(grid.numpy(), mlp.numpy(), L)(x - np.array([0, 0, h]) * k[:, None])
+    assert np.median(np.abs(moved - ref)[k == 1] / np.abs(ref)[k == 1]) > 10 * FWD_TOL
+    check_close("lattice phi", got, ref, FWD_TOL)

@@ -167,3 +167,85 @@ def test_kernel_times_do_not_overlap():
     print(times, flush=True)
     assert times["field"] > 0 and times["scatter"] > 0
     assert times["field"] + times["scatter"] <= times["call"]
+
+
+@pytest.mark.parametrize("counted", [False, True])
+def test_ray_gradients_through_records(counted):
+    """Pose refinement's dL/do and dL/dr, with the grid's gradient scattered
+    through records: decided by the host, and by the count on the device."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=1250, S=777, grid_std=0.3)
+    b = _clear(grid, mlp, L, b)
+    assert len(b.t) + 2 * len(b.xs) >= records_from(L)
+    db = _padded(b, 2 * len(b.t)) if counted else G.RayBatch.from_host(b)
+    go, gr = torch.zeros(db.M, 3, device="cuda"), torch.zeros(db.M, 3, device="cuda")
+    gg, gm = _gradients(G.make_model(L), db, grid, mlp, go, gr)
+    cfg = ostep.LossCfg(lambdas=LAMBDAS)
+    ref = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, cfg, ray_grads=True)
+    r32 = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, cfg, ray_grads=True, dtype=torch.float32)
+    for name, got, key in (("dL/do", go.cpu().numpy(), "grad_o"), ("dL/dr", gr.cpu().numpy(), "grad_r"),
+                           ("grad_grid", gg, "grad_grid"), ("grad_mlp", gm, "grad_mlp")):
+        check_parity(name, got, _np(ref[key]), _np(r32[key]), GRAD_TOL)
+
+
+def test_colour_grid_with_records():
+    from tests.test_gpu_colour import _device, clear_of_kinks
+    L, fr, b, grid, mlp = sphere_case(M=1250, S=777, grid_std=0.3)
+    cg, cm = synth.init_colour(L, seed=2, grid_std=0.5)
+    kw = dict(colour_grid=cg.numpy(), colour_mlp=cm.numpy())
+    b, _, _ = clear_of_kinks(grid.numpy(), mlp.numpy(), L, b, **kw)
+    assert len(b.t) + 2 * len(b.xs) >= records_from(L)
+    ref = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, **kw)
+    r32 = ostep.evaluate(grid.numpy(), mlp.numpy(), L, b, dtype=torch.float32, **kw)
+    dev = _device(L, b, grid, mlp, cg, cm)
+    for name, key in (("grad_grid", "grad_grid"), ("grad_mlp", "grad_mlp"), ("grad_cg", "grad_colour_grid"),
+                      ("grad_cm", "grad_colour_mlp")):
+        check_parity(key, dev[name], _np(ref[key]), _np(r32[key]), GRAD_TOL)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("lambdas", [LAMBDAS, LAMBDAS[:4] + (0.0, 0.0), (0.0, 0.0, 0.0, 0.0, 1.0, 0.0)])
+@pytest.mark.parametrize("lens", ["even", "ragged"])
+def test_records_equal_the_direct_scatter(bf16, lambdas, lens):
+    """The same batch with the records' room in the workspace and without it: the
+    gradients agree up to the order of float32 additions (a sum of n addends of
+    one size is off by about sqrt(n) 2^-24 of it; the bound leaves n = 10^4), and
+    the same entries are reached.  The workspace is dirty, and holds another
+    batch's records when the batch comes a second time."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=1600, S=777, grid_std=0.3)
+    _, _, other, _, _ = sphere_case(M=1600, S=777, seed=8, grid_std=0.3)
+    if lens == "ragged":   # empty rays, rays of 1 to 256 samples, rays past the cap of 256
+        rng = np.random.default_rng(2)
+        n = rng.integers(0, 140, 1600)
+        n[:6] = (0, 1, 256, 257, 300, 0)
+        t = np.concatenate([np.sort(rng.uniform(0.1, 3.0, k)) for k in n]).astype(np.float32)
+        seg = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+        b = ostep.Batch(b.o, b.r, b.rgb, b.depth, t, seg, b.xs, b.eps)
+    model = G.make_model(L, G.BF16 if bf16 else G.FP32)
+    lc = G.make_loss_cfg(lambdas)
+    db, do = G.RayBatch.from_host(b), G.RayBatch.from_host(other)
+    assert db.total >= records_from(L) and do.total >= records_from(L)
+    g, m = grid.cuda().contiguous(), mlp.cuda().contiguous()
+    bf = None
+    if bf16:
+        bf = torch.empty(g.shape, dtype=torch.bfloat16, device="cuda")
+        G.gosurf_refresh_bf16(g, bf)
+    ws = torch.full((max(G.gosurf_workspace_bytes(model, x.M, x.total, x.S) for x in (db, do)),), 0xFF,
+                    device="cuda", dtype=torch.uint8)
+    need = G.lib().gosurf_workspace_bytes(None, db.M, db.total, db.S)
+
+    def run(batch, w):
+        out = G.gosurf_forward(model, g, m, batch, lc, w, grid_bf16=bf)
+        gg, gm = torch.zeros_like(g), torch.zeros_like(m)
+        G.gosurf_backward(model, g, m, batch, lc, out, 1.0, gg, gm, w, grid_bf16=bf)
+        torch.cuda.synchronize()
+        return gg.double(), gm.double()
+
+    ref = run(db, ws[:need])
+    runs = [run(db, ws), run(do, ws), run(db, ws)]
+    for got in (runs[0], runs[2]):
+        for a, r in zip(got, ref):
+            assert float((a - r).norm()) <= 1e-6 * float(r.norm())
+            assert float((a - r).abs().max()) <= 1e-5 * float(r.abs().max())
+        assert torch.equal(got[0] != 0, ref[0] != 0)
