@@ -345,8 +345,8 @@ typedef struct {
    samples each. */
 size_t gosurf_importance_workspace_bytes(int32_t M, int32_t n_coarse, const gosurf_importance_cfg* cfg);
 
-/* The full sampler: the SDF of the coarse samples (the forward field kernel,
-   at the model's precision), then `steps` times one importance step, the SDF
+/* The full sampler: the SDF of the coarse samples (at the model's precision),
+   then `steps` times one importance step, the SDF
    at the new samples and the merge.  `coarse` must hold the same number n0 of
    sorted samples on every ray (a batch of gosurf_sample_rays without a
    proposal: total = M * n0).  Writes out->t [M * nf], out->seg [M + 1] and

@@ -284,8 +284,6 @@ struct ImpMergeArgs {
   int* seg_out;          // [M + 1] or null
 };
 
-// Surface extraction: lattice rows as rays for the forward field kernel, and
-// marching tetrahedra over the SDF lattice.
 // SDF alone, of ray samples (t, ray_of) or, without them, of lattice points
 // p0 + h (i, j, k), x fastest, z layers from k0 on.
 struct PhiArgs {
@@ -303,6 +301,7 @@ struct PhiArgs {
   float h;
   int nx, ny, k0;
 };
+// Marching tetrahedra over the SDF lattice.
 struct MtArgs {
   const float* phi;         // [nz][ny][nx]
   float p0[3];

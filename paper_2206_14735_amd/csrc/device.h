@@ -90,22 +90,19 @@ __device__ __forceinline__ float log_sigmoid(float x) {
 }
 // a / b for b in [1, 2] and 0 <= a <= 1: no operand needs scaling, so a
 // reciprocal, one Newton step and one residual correction replace the general
-// division (6 instructions instead of 11); within an ulp of the exact quotient.
+// division (6 instructions instead of 11).  Correctly rounded for the sigmoid's
+// operands: of all float32 e in (0, 1], none of 1 / (1 + e) and e / (1 + e) is off.
 __device__ __forceinline__ float div_near_one(float a, float b) {
   float y = __builtin_amdgcn_rcpf(b);
   y = fmaf(fmaf(-b, y, 1.f), y, y);
   const float q = a * y;
   return fmaf(fmaf(-b, q, a), y, q);
 }
-// ROUNDED: the quotient correctly rounded (where it goes on into BF16 operands,
-// which a last bit can move by 2^-9).
-template <bool ROUNDED = false>
 __device__ __forceinline__ float sigmoidf_(float x) {
   // 1 / (1 + e^-x) or e^x / (1 + e^x), whichever does not overflow: one
   // exponential and one division for both
   const float e = __expf(-fabsf(x));
-  if constexpr (ROUNDED) return (x >= 0.f ? 1.f : e) / (1.f + e);
-  else return div_near_one(x >= 0.f ? 1.f : e, 1.f + e);
+  return div_near_one(x >= 0.f ? 1.f : e, 1.f + e);
 }
 __device__ __forceinline__ float signf_(float x) { return x > 0.f ? 1.f : (x < 0.f ? -1.f : 0.f); }
 

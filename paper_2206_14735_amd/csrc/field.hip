@@ -426,7 +426,7 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
     layer<BF, 1, 2>(sm, T_C2, hc, &cb, lane);
     cb = plus_bias(cb, sm.bias + 112, q);
 #pragma unroll
-    for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_<BF>(cb[r]);   // rows 0..2 of group 0 are used
+    for (int r = 0; r < 3; ++r) cb[r] = sigmoidf_(cb[r]);   // rows 0..2 of group 0 are used
   } else {
     cb = v4f{0.f, 0.f, 0.f, 0.f};
   }
