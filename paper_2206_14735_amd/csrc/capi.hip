@@ -535,6 +535,10 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
     return fail(GOSURF_ERR_NULL, "grads.ray_o and grads.ray_r are both given or both NULL");
   if (!aligned(grads->grid, 16)) return fail(GOSURF_ERR_ALIGN, "grads.grid must be 16-byte aligned");
   if (!std::isfinite(loss_scale)) return fail(GOSURF_ERR_VALUE, "loss_scale must be finite");
+  const bool ray_grads = grads->ray_o != nullptr;
+  const bool cgrid = model->colour_mode == GOSURF_COLOUR_GRID;
+  if (cgrid && ray_grads)
+    return fail(GOSURF_ERR_VALUE, "ray gradients (pose refinement) are not built for the colour-grid path");
   const long long copy_bytes = model_copy_bytes(model);
   if (copy_bytes < 0)
     return fail(GOSURF_ERR_VALUE, "gradient copies need levels of at most 2048 x 2048 x 512 vertices and 2^31 floats");
@@ -584,14 +588,10 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.o = b->o; fa.r = b->r; fa.t = b->t; fa.ray_of = b->ray_of; fa.total = b->total;
   fa.xs = b->xs; fa.eps = b->eps; fa.S = S; fa.seg_end = b->seg + b->M;
   fa.seed4 = w.seed4; fa.posw = w.posw; fa.need_gx = need_gx;
-  const bool ray_grads = grads->ray_o != nullptr;
-  const bool cgrid = model->colour_mode == GOSURF_COLOUR_GRID;
   fa.colour = !cgrid;
   // dL/dx per sample replaces the sample's seeds once read (the colour kernel,
   // which also reads the seeds, runs first then)
   fa.grad_x = ray_grads ? w.seed4 : nullptr;
-  if (cgrid && ray_grads)
-    return fail(GOSURF_ERR_VALUE, "ray gradients (pose refinement) are not built for the colour-grid path");
   fa.rec = rec; fa.grad_grid = grads->grid; fa.mlp_partial = w.mlp_partial;
   fa.priv_partial = w.priv_partial;
   fa.smooth_coef = b->S > 0 ? 2.f * loss->lambda[5] * loss_scale / (float)b->S : 0.f;

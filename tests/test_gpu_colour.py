@@ -133,3 +133,24 @@ def test_second_sample_of_a_tile_in_the_first_cell():
     check_parity("grad colour grid", dev["grad_cg"], _np(ref["grad_colour_grid"]), _np(r32["grad_colour_grid"]),
                  GRAD_TOL)
     assert np.all(dev["grad_cg"][_np(ref["grad_colour_grid"]) == 0] == 0)
+
+
+def test_a_refused_backward_enqueues_nothing():
+    """Ray gradients are not built for the colour-grid path: the call is refused
+    before anything is enqueued, so the workspace stays as it was."""
+    G = _G()
+    L, fr, b, grid, mlp = sphere_case(M=8, S=0, grid_std=0.2)
+    cg, cm = (x.cuda() for x in synth.init_colour(L, seed=2, grid_std=0.5))
+    db, lc = G.RayBatch.from_host(b), G.make_loss_cfg()
+    model = G.make_model(L, colour_mode=G.COLOUR_GRID)
+    ws = G.workspace_for(model, db.M, db.total, db.S)
+    g, m = grid.cuda(), mlp.cuda()
+    out = G.gosurf_forward(model, g, m, db, lc, ws, colour_grid=cg, colour_mlp=cm)
+    ws.fill_(0x5A)
+    with pytest.raises(G.GosurfError, match="colour-grid"):
+        G.gosurf_backward(model, g, m, db, lc, out, 1.0, torch.zeros_like(g), torch.zeros_like(m), ws,
+                          grad_o=torch.zeros(8, 3, device="cuda"), grad_r=torch.zeros(8, 3, device="cuda"),
+                          colour_grid=cg, colour_mlp=cm, grad_colour_grid=torch.zeros_like(cg),
+                          grad_colour_mlp=torch.zeros_like(cm))
+    torch.cuda.synchronize()
+    assert bool((ws == 0x5A).all())
