@@ -75,9 +75,10 @@ void plan_bins(const Grid& g, Bins& B) {
 //   64 bins, no pairs: 33 k 53 / 68, 66 k 72 / 80, 77 k 82 / 85, 96 k 98 / 90,
 //     131 k 123 / 100; 4096 pairs: 74 k 91 / 85, 91 k 103 / 91
 //   125 bins: 64 k 74 / 87, 128 k 118 / 103, 192 k 166 / 122
-// The lines lie where the two meet in FP32.  BF16 decoders leave more of the
-// direct adds uncovered, and records win earlier there (0.59 M at 3 cm: 356 / 306,
-// 1.57 M at 2 cm: 822 / 716): one line serves both, on the safe side.
+// The lines lie where the two meet in FP32, a little above it at 3 cm, where they
+// run side by side from 1.5 to 2 M.  BF16 decoders leave more of the direct adds
+// uncovered, and records win earlier there (0.59 M at 3 cm: 356 / 306, 1.57 M at
+// 2 cm: 822 / 716): one line serves both, on the safe side.
 long long records_from(const Bins& B, int far) {
   const long long bins = (long long)B.nb[0] * B.nb[1] * B.nb[2];
   if (bins <= 256) return 50000 + 256 * bins;
