@@ -813,7 +813,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !
 // a dot product (8 multiply-adds and two row swaps in place of 8 MFMAs of 32 cycles).
 // The sampler does not: its draws magnify the last bit of the SDF, so it reads the
 // one that the render computes.
-// MI355X, us: 288 x 224 x 128 points 585 in all launches -> 338 in one; 96 and 3 x
+// MI355X, us: 288 x 224 x 128 points 585 in all launches -> 346 in one; 96 and 3 x
 // 12 samples of 6144 rays 93 -> 75.  Four waves per SIMD, as the compiler chooses,
 // hold the tables in registers: two or three take 10 % longer, five or more 25 %.
 template <bool BF, bool ROW>
