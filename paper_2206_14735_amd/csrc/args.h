@@ -18,9 +18,9 @@ struct EdgeCheck {
 
 // Whether a backward pass scatters through records.  The host decides by the
 // number of samples where it knows it.  Of a batch drawn with a proposal it knows
-// the capacity, up to three times the samples there are; where the capacity
-// would do, the kernels of both ways are launched, and each decides by the
-// count on the device (all read the same) whether it runs or ends at once.
+// the capacity, up to three times the samples there are; where that leaves it
+// open, the kernels of both ways are launched, and each decides by the count on
+// the device (all read the same) whether it runs or ends at once.
 struct RecordChoice {
   const int* seg_end;   // sample count on the device, or nullptr: the host's word holds
   int records;

@@ -19,7 +19,7 @@ LevelSums small_sums(const Grid& g, const ScatterRecords& r);
 void plan_privatised_levels(FieldArgs& a, int counts[4]);
 int priv_max_floats();
 void plan_bins(const Grid& g, Bins& b);
-long long records_from(const Bins& b, int far);
+long long records_from(const Bins& b, int far, bool bf16, bool ragged);
 long long plan_tables(const Grid& g, ScatterRecords& r, float* tables);
 long long max_tables();
 hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st);
@@ -295,7 +295,8 @@ size_t gosurf_workspace_bytes(const gosurf_model* model, int32_t M, int32_t tota
   gs::plan_privatised_levels(fa, counts);
   gs::Bins bins;
   gs::plan_bins(fa.g, bins);
-  const bool records = total + 2LL * S >= gs::records_from(bins, 4 - __builtin_popcount(fa.priv_mask));
+  const bool records = total + 2LL * S >= gs::records_from(bins, 4 - __builtin_popcount(fa.priv_mask),
+                                                           model->precision == GOSURF_BF16, false);
   return records && w.with_records > need ? w.with_records : need;
 }
 
@@ -565,12 +566,16 @@ gosurf_status gosurf_backward(const gosurf_model* model, const gosurf_params* pa
   fa.g = g;
   int counts[4];
   gs::plan_privatised_levels(fa, counts);
-  const long long from = gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask)) - 2LL * S;
-  const bool records = b->total >= from && ws_bytes >= w.with_records;
-  // a batch with prop may hold fewer samples than `total`: its count decides, and
-  // both ways are launched
-  const bool counted = records && b->prop != nullptr;
-  const bool direct = !records || counted;
+  // A batch with prop holds about a third of `total` samples: its count decides,
+  // and both ways are launched.  The way not taken costs about 11 us (6144 BF16
+  // rays, 153 us), so that the arrays must have room for twice the samples that
+  // records begin with.
+  bool ragged = b->prop != nullptr;
+  const long long from = gs::records_from(rec.bins, 4 - __builtin_popcount(fa.priv_mask),
+                                          model->precision == GOSURF_BF16, ragged) - 2LL * S;
+  if (from <= 0) ragged = false;   // the pairs alone decide
+  const bool records = b->total >= (ragged ? 2 * from : from) && ws_bytes >= w.with_records;
+  const bool counted = records && ragged, direct = !records || counted;
   if (records) {
     rec.choice.records = 1; rec.choice.total = b->total; rec.choice.from = from > 0 ? (int)from : 0;
     rec.choice.seg_end = counted ? b->seg + b->M : nullptr;

@@ -674,8 +674,6 @@ __device__ __forceinline__ void field_tile(const FieldArgs& A, const Smem& sm, i
 // wave's only add to their queue (65536 x 96: 3.21 ms with two, 3.35 with three).
 template <bool BWD, bool BF, bool POSE, bool REC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !POSE ? 3 : 2))) void field_kernel(FieldArgs A) {
-  if constexpr (BWD)
-    if (A.rec.choice() != REC) return;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   FieldSmem<BF, BWD, REC>& sm = *reinterpret_cast<FieldSmem<BF, BWD, REC>*>(smem_raw);
   const int tid = threadIdx.x;
@@ -702,6 +700,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(REC && !
   float* priv = reinterpret_cast<float*>(smem_raw + smem_bytes<BF, BWD, REC>());
   if (BWD && !REC)
     for (int e = tid; e < A.priv_floats; e += kBlock) priv[e] = 0.f;
+  if constexpr (BWD)
+    if (A.rec.choice() != REC) return;   // (here its arguments arrive behind the tables' loads)
   __syncthreads();
 
   // the device sample count never exceeds the capacity the workspace and the

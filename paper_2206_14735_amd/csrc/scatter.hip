@@ -57,11 +57,15 @@ void plan_bins(const Grid& g, Bins& B) {
   B.inv_v = 1.f / g.voxel[f];
 }
 
+// Grids so small that many samples share every vertex.
+static bool few_bins(long long bins) { return bins <= 256; }
+
 // The points (samples and pair points) from which a batch is scattered through
 // records.  Without them the field kernel adds to memory itself, about 8 requests
 // per sample overlapped with its decoders; with them it writes records of up to
 // 160 bytes, and the scatter's time comes on top, with a share for every bin that
-// is touched.  `far`: levels the field kernel would not accumulate in LDS.
+// is touched.  `far`: levels the field kernel would not accumulate in LDS;
+// `ragged`: most rays have their samples about the surface (a proposal drew them).
 // Measured (MI355X, backward call, us, direct / records), 96 samples per ray and
 // 16384 pairs unless stated:
 //   room at 3 cm, 16128 bins: 0.59 M samples 352 / 388, 1.57 M 820 / 803,
@@ -75,15 +79,22 @@ void plan_bins(const Grid& g, Bins& B) {
 //   64 bins, no pairs: 33 k 53 / 68, 66 k 72 / 80, 77 k 82 / 85, 96 k 98 / 90,
 //     131 k 123 / 100; 4096 pairs: 74 k 91 / 85, 91 k 103 / 91
 //   125 bins: 64 k 74 / 87, 128 k 118 / 103, 192 k 166 / 122
+//   64 bins, rays of 24 samples about the surface, whose runs merge before they are
+//     added: 104 k 82 / 93, 177 k 114 / 128, 323 k 178 / 171
 // The lines lie where the two meet in FP32, a little above it at 3 cm, where they
-// run side by side from 1.5 to 2 M.  BF16 decoders leave more of the direct adds
-// uncovered, and records win earlier there (0.59 M at 3 cm: 356 / 306, 1.57 M at
-// 2 cm: 822 / 716): one line serves both, on the safe side.
-long long records_from(const Bins& B, int far) {
+// run side by side from 1.5 to 2 M.  BF16 decoders take less time to cover the
+// direct adds with, and the two meet earlier:
+//   3 cm, no pairs: 0.39 M 235 / 238, 0.59 M 328 / 296, 1.57 M 801 / 587; rays of
+//     24 or 96 samples: 0.36 M 209 / 216, 0.60 M 300 / 283, 2.4 M 954 / 775
+//   2 cm, no pairs: 0.79 M 429 / 502, 1.57 M 822 / 716; 1 cm: 6.3 M 3395 / 3576
+// On small grids the two precisions share a line, and two levels in LDS keep BF16
+// direct too, where the sides meet at 1.3 M.
+long long records_from(const Bins& B, int far, bool bf16, bool ragged) {
   const long long bins = (long long)B.nb[0] * B.nb[1] * B.nb[2];
-  if (bins <= 256) return 50000 + 256 * bins;
+  if (few_bins(bins)) return (ragged ? 4 : 1) * (50000 + 256 * bins);
   if (far < 3) return 1LL << 62;
-  return 48 * bins > (1LL << 21) ? 48 * bins : 1LL << 21;
+  const long long per_bin = (bf16 ? 24 : 48) * bins, least = bf16 ? 1LL << 19 : 1LL << 21;
+  return per_bin > least ? per_bin : least;
 }
 
 // Slots of the counting table (about 2^14 for grids of fewer bins, see
@@ -511,18 +522,23 @@ hipError_t launch_bin_first(const ScatterRecords& r, hipStream_t st) {
 // At most one resident round of waves: 9 windows with their staging fit the
 // 160 KB of a CU (the occupancy query's answer too; sized for 8, ragged BF16 rays
 // take 2.5 % longer).  The kernel takes its chunks from the records there are, which
-// may be fewer than the arrays hold.
+// may be fewer than the arrays hold: four a wave, or two (as for half the waves) on
+// small grids, whose bins are alike and whose windows queue at the same addresses
+// (64 bins, 1 M samples: 435 us with four, 399 with two; 1.2 M in BF16 at 3 cm: 475
+// and 529).
 hipError_t launch_scatter(const ScatterArgs& a, hipStream_t st) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const long long tiles = (a.rec.cap + 15) / 16, waves = (9LL * cus + kQueues - 1) / kQueues * kQueues;
-  const long long chunk = scatter_chunk((unsigned)tiles, (unsigned)waves);
+  const Bins& b = a.rec.bins;
+  const long long share = few_bins((long long)b.nb[0] * b.nb[1] * b.nb[2]) ? waves / 2 : waves;
+  const long long chunk = scatter_chunk((unsigned)tiles, (unsigned)share);
   long long blocks = (tiles + chunk - 1) / chunk;
   if (blocks > waves) blocks = waves;   // a multiple of kQueues, as drawing needs
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)waves);
+  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)blocks), dim3(64), 0, st, a, (int)share);
   return hipGetLastError();
 }
 

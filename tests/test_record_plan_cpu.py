@@ -46,7 +46,7 @@ def _plan(voxels, size):
     return _bins([0.0] * 3, size, voxels, dims)
 
 
-def records_from(layout):
+def records_from(layout, bf16=False, ragged=False):
     """Points (samples, and two per smoothness pair) from which a batch on this
     layout is scattered through records."""
     b = _bins(layout.p0, layout.p1, layout.voxels, layout.dims)
@@ -57,9 +57,9 @@ def records_from(layout):
             kept += n
         else:
             far += 1
-    f = G.lib()._ZN2gs12records_fromERKNS_4BinsEi
+    f = G.lib()._ZN2gs12records_fromERKNS_4BinsEibb
     f.restype = C.c_longlong
-    return f(C.byref(b), far)
+    return f(C.byref(b), far, C.c_bool(bf16), C.c_bool(ragged))
 
 
 @pytest.mark.parametrize("thin", [0, 1, 2, None])
@@ -82,7 +82,7 @@ def test_windows_fit_the_lds_and_the_flush(thin):
         assert b.shift >= 2
 
 
-# Backward times on MI355X in FP32, us: (voxels coarsest first, box, samples, pairs, direct, through records)
+# Backward times on MI355X, us: (voxels, box, samples, pairs, direct, through records)
 ROOM, CUBE = ((0.0, 0.0, 0.0), (8.0, 6.0, 3.0)), ((-1.0,) * 3, (1.0,) * 3)
 MEASURED = [
     ((0.03, 0.06, 0.24, 0.96), ROOM, 589824, 16384, 352, 388), ((0.03, 0.06, 0.24, 0.96), ROOM, 1248000, 0, 631, 662),
@@ -96,7 +96,18 @@ MEASURED = [
 ]
 
 
-@pytest.mark.parametrize("voxels,box,samples,pairs,direct,records", MEASURED)
-def test_records_are_taken_where_they_were_faster(voxels, box, samples, pairs, direct, records):
+MEASURED_BF16 = [
+    ((0.03, 0.06, 0.24, 0.96), ROOM, 393216, 0, 235, 238), ((0.03, 0.06, 0.24, 0.96), ROOM, 589824, 16384, 356, 306),
+    ((0.03, 0.06, 0.24, 0.96), ROOM, 361968, 16384, 209, 216), ((0.03, 0.06, 0.24, 0.96), ROOM, 2097152, 16384, 1098, 746),
+    ((0.02, 0.06, 0.24, 0.96), ROOM, 786432, 0, 429, 502), ((0.02, 0.06, 0.24, 0.96), ROOM, 1572864, 0, 822, 716),
+    ((0.01, 0.06, 0.24, 0.96), ROOM, 6291456, 0, 3395, 3576),
+    ((0.08, 0.16, 0.32, 0.64), CUBE, 32768, 0, 53, 65), ((0.08, 0.16, 0.32, 0.64), CUBE, 76800, 0, 81, 77),
+    ((0.05, 0.1, 0.2, 0.4), CUBE, 64000, 0, 74, 84), ((0.05, 0.1, 0.2, 0.4), CUBE, 128000, 0, 119, 90),
+]
+
+
+@pytest.mark.parametrize("bf16,voxels,box,samples,pairs,direct,records",
+                         [(False, *m) for m in MEASURED] + [(True, *m) for m in MEASURED_BF16])
+def test_records_are_taken_where_they_were_faster(bf16, voxels, box, samples, pairs, direct, records):
     layout = synth.padded_layout(*box, voxels)
-    assert (samples + 2 * pairs >= records_from(layout)) == (records < direct)
+    assert (samples + 2 * pairs >= records_from(layout, bf16)) == (records < direct)
