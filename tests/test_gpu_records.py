@@ -249,3 +249,48 @@ def test_records_equal_the_direct_scatter(bf16, lambdas, lens):
             assert float((a - r).norm()) <= 1e-6 * float(r.norm())
             assert float((a - r).abs().max()) <= 1e-5 * float(r.abs().max())
         assert torch.equal(got[0] != 0, ref[0] != 0)
+
+
+def test_a_captured_step_follows_the_count():
+    """Forward and backward of a batch with `prop`, captured once and replayed on
+    batches of other sample counts in the same arrays, on both sides of the count
+    from which records are taken, with eager work and synchronisations between the
+    replays: each replay gives what the eager calls give."""
+    from paper_2206_14735_amd import gosurf as G
+    L, fr, b, grid, mlp = sphere_case(M=4250, S=777, grid_std=0.3)
+    line = records_from(L, ragged=True) - 2 * len(b.xs)
+    full = _padded(b, 2 * len(b.t))
+    assert len(b.t) >= line and full.total >= 2 * line
+    seg_all = full.seg.clone()
+    model, lc = G.make_model(L), G.make_loss_cfg(LAMBDAS)
+    g, m = grid.cuda().contiguous(), mlp.cuda().contiguous()
+    ws = G.workspace_for(model, full.M, full.total, full.S)
+    out = G.FwdOut.empty(full.M, full.total, "cuda")
+    gg, gm = torch.zeros_like(g), torch.zeros_like(m)
+
+    def step():
+        gg.zero_()
+        gm.zero_()
+        G.gosurf_forward(model, g, m, full, lc, ws, out=out)
+        G.gosurf_backward(model, g, m, full, lc, out, 1.0, gg, gm, ws)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for n in (len(b.t), line, line - 1, 5000, len(b.t), line - 1):
+        full.seg.copy_(seg_all.clamp(max=n))
+        ws.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = gg.double().clone(), gm.double().clone(), out.losses.clone()
+        ws.fill_(0x5A)
+        step()
+        torch.cuda.synchronize()
+        assert torch.equal(got[2], out.losses), n
+        for a, r in zip(got, (gg.double(), gm.double())):
+            assert float((a - r).norm()) <= 1e-6 * float(r.norm()), n
